@@ -25,9 +25,8 @@ enum Program { P_CONST = 0, P_LINEAR = 1, P_QUAD = 2, P_INVDIST = 3, P_VERTEX = 
 // caller's primitive id (bits 0..28) and its boundary kind (bits 29..30).
 // --------------------------------------------------------------------------
 // The BVH is stored as 4-wide interior records: the host collapses the binary
-// SAH tree (a record takes its node's two children and opens the largest
-// interior ones until it holds four entries), so a line takes half the
-// dependent record fetches of a binary tree and one record is one 64-byte
+// SAH tree so that a line fetches the fewest records (wob.hip, Collapse), about
+// half the dependent fetches of a binary tree, and one record is one 64-byte
 // line.  The traversal is bound by the rate at which the CUs' vector memory
 // path serves the lanes' gathers, so records are kept small: in an FP32 scene
 // the boxes are binary16 in a normalised frame (scene centre c, power-of-two
@@ -35,8 +34,9 @@ enum Program { P_CONST = 0, P_LINEAR = 1, P_QUAD = 2, P_INVDIST = 3, P_VERTEX = 
 // reads them with mixed-precision FMAs.  A child entry is the index of an
 // interior record (>= 0) or a leaf, -1 - ((first << 3) | (count - 1)) with
 // first the leaf-order index of its first primitive (< 2^27).  Unused slots
-// hold an empty box (lo > hi), which no line crosses.
+// hold a box of NaN, which no line crosses.
 constexpr int kArity = 4;
+constexpr int kLeafPrims = 2;  // most primitives in a leaf
 template <typename R> struct alignas(32) Wide { R lo[kArity][3], hi[kArity][3]; int32_t child[kArity]; };
 // FP32 scenes: one word per box and axis, binary16 lo in the low half and hi
 // in the high half.  A lane rotates each word by 16 bits when its direction is
@@ -44,21 +44,18 @@ template <typename R> struct alignas(32) Wide { R lo[kArity][3], hi[kArity][3]; 
 // half its far side without a min / max per axis.  (2D scenes leave the third
 // axis word unused.)
 template <> struct alignas(64) Wide<float> { uint32_t box[kArity][3]; int32_t child[kArity]; };
-// Traversal positions besides entries: take the next entry from the stack,
-// and the line's traversal is over.
-constexpr int32_t kPop = INT32_MIN;
-constexpr int32_t kDone = INT32_MAX;
-// Bound on the traversal stack: a record pushes the crossed entries it does
-// not continue with (up to three), so a lane's stack never holds more than the
-// largest sum of (entries - 1) over the records on a root-to-leaf path, which
-// the scene upload computes (scenes above this bound are rejected); with the
-// leaf queue a lane's LDS stays within 64 entries, a 256-thread workgroup's
-// within 64 KB.
+// The entry below all others on a line's stack: its traversal is over.
+constexpr int32_t kEnd = INT32_MAX;
+// Bound on the traversal stack.  Only crossed records wait on it (crossed
+// leaves go to the lane's leaf slots): a lane never holds more than the
+// largest sum, over a root-to-leaf path, of the records that are taken after
+// the path's own, which the scene upload computes and keeps small by the order
+// of the slots (scenes above this bound are rejected).
 constexpr int kMaxDepth = 60;
-// An FP32 triangle record is padded to 64 bytes so that it never straddles a
-// 64-byte block: the traversal is bound by the rate of L1-miss requests, and a
-// straddling record costs two.
-template <typename R> struct alignas(sizeof(R) == 4 ? 64 : 32) Prim3 { R v0[3]; int32_t idkind; R e1[3]; R alpha; R e2[3]; int32_t pad; };
+// FP32 triangle records lie 48 bytes apart in small scenes, and 64 in large
+// ones, where each then holds its unit normal in the last 16 bytes and never
+// straddles a 64-byte block (see prim_layout in the scene upload).
+template <typename R> struct alignas(sizeof(R) == 4 ? 16 : 32) Prim3 { R v0[3]; int32_t idkind; R e1[3]; R alpha; R e2[3]; int32_t pad; };
 template <typename R> struct alignas(16) Prim2 { R v0[2]; R e[2]; R alpha; int32_t idkind; };
 
 template <typename R, int D> struct Rec;
@@ -71,8 +68,11 @@ constexpr int32_t kIdMask = (1 << kIdBits) - 1;
 template <typename R, int D>
 struct SceneView {
   const typename Rec<R, D>::Node* nodes;
-  const typename Rec<R, D>::Prim* prims;
-  const R* normals;           // 4 per primitive (leaf order): unit outward normal, 0
+  // primitive records and unit outward normals (4 values, the last 0) in leaf
+  // order, each a fixed number of bytes apart
+  const char* prims;
+  const char* normals;
+  uint32_t prim_stride, normal_stride;
   const int32_t* leaf_of_id;  // caller id -> leaf-order index
   const float* area_cdf;      // caller-id order, cumulative area / |Gamma| (binary32, last 1)
   // guide[b] = the first index whose area_cdf exceeds b / 2^guide_shift
@@ -83,7 +83,7 @@ struct SceneView {
   int32_t n_nodes;            // interior records
   int32_t n_prims;
   int32_t root;               // entry of the root: record 0, or a leaf when the tree is one leaf
-  int32_t stack_cap;          // traversal stack entries per lane (the tree depth, >= 1)
+  int32_t stack_cap;          // most records that wait on a lane's traversal stack (>= 1)
   R fc[3], fk;                // frame of the boxes: y' = (y - fc) fk (fc[2] = 0 in 2D)
 };
 
@@ -190,9 +190,15 @@ struct PrimGeo {
 };
 
 template <typename R, int D>
-__device__ __forceinline__ PrimGeo<R> load_prim(const SceneView<R, D>& s, int32_t idx) {
+__device__ __forceinline__ const typename Rec<R, D>::Prim& prim_record(const char* prims, uint32_t stride,
+                                                                         int32_t idx) {
+  return *reinterpret_cast<const typename Rec<R, D>::Prim*>(prims + (uint64_t)(uint32_t)idx * stride);
+}
+
+template <typename R, int D>
+__device__ __forceinline__ PrimGeo<R> load_prim(const char* prims, uint32_t stride, int32_t idx) {
   PrimGeo<R> g;
-  const auto& p = s.prims[idx];
+  const auto& p = prim_record<R, D>(prims, stride, idx);
   if constexpr (D == 3) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -211,12 +217,17 @@ __device__ __forceinline__ PrimGeo<R> load_prim(const SceneView<R, D>& s, int32_
   return g;
 }
 
+template <typename R, int D>
+__device__ __forceinline__ PrimGeo<R> load_prim(const SceneView<R, D>& s, int32_t idx) {
+  return load_prim<R, D>(s.prims, s.prim_stride, idx);
+}
+
 // Unit normal pointing out of Omega.  Computed on the host in binary64 from
 // the rounded vertices and stored once: the cross product of two short edges
 // of a sliver triangle is too ill-conditioned to normalise in binary32.
 template <typename R, int D>
 __device__ __forceinline__ void load_normal(const SceneView<R, D>& s, int32_t idx, R n[3]) {
-  const R* p = s.normals + 4 * (int64_t)idx;
+  const R* p = reinterpret_cast<const R*>(s.normals + (uint64_t)(uint32_t)idx * s.normal_stride);
   n[0] = p[0];
   n[1] = p[1];
   n[2] = D == 3 ? p[2] : (R)0;
@@ -497,17 +508,17 @@ __device__ __forceinline__ R plane_hit(const PrimGeo<R>& g, const R n[3], const 
 
 // Slab test of a line against a box in the scene's box frame; inv = 1 / d
 // (finite), ox = -x' inv with x' the line's point in that frame.  The near side
-// of each slab is lo where inv >= 0 and hi otherwise, so an empty box (lo above
-// hi, an unused record slot) is never crossed.
+// of each slab is lo where inv >= 0 and hi otherwise; a box of NaN (an unused
+// record slot) is never crossed.
 template <typename R, int D>
 __device__ __forceinline__ bool line_box(const R lo[3], const R hi[3], const R inv[3], const R ox[3]) {
-  R tmin = (R)-INFINITY, tmax = (R)INFINITY;
+  R tmin, tmax;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const bool pos = inv[k] >= (R)0;
     const R tn = fma(pos ? lo[k] : hi[k], inv[k], ox[k]), tf = fma(pos ? hi[k] : lo[k], inv[k], ox[k]);
-    tmin = fmax(tmin, tn);
-    tmax = fmin(tmax, tf);
+    tmin = k == 0 ? tn : fmax(tmin, tn);
+    tmax = k == 0 ? tf : fmin(tmax, tf);
   }
   return tmin <= tmax;
 }
@@ -522,7 +533,9 @@ template <typename R> __device__ __forceinline__ R safe_inv(R d) {
 }
 
 // Slab-test constants of the line x + t d: inv = 1 / d, ox = -x' inv, and
-// the rotation that puts a packed box word's near side in its low half.
+// the rotation that puts a packed box word's near side in its low half.  The
+// box test asks whether the whole line crosses, so the sign of t is free: it is
+// taken such that inv[0] > 0, and the first axis needs no rotation.
 template <typename R, int D>
 __device__ __forceinline__ void line_slabs(const SceneView<R, D>& s, const R x[3], const R d[3], R inv[3],
                                            R ox[3], uint32_t rot[3]) {
@@ -530,6 +543,12 @@ __device__ __forceinline__ void line_slabs(const SceneView<R, D>& s, const R x[3
   for (int k = 0; k < 3; ++k) {
     inv[k] = safe_inv(d[k]);
     ox[k] = -((x[k] - s.fc[k]) * s.fk) * inv[k];
+  }
+  const R sg = inv[0] < (R)0 ? (R)-1 : (R)1;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    inv[k] *= sg;
+    ox[k] *= sg;
     rot[k] = inv[k] < (R)0 ? 16u : 0u;
   }
 }
@@ -543,7 +562,8 @@ __device__ __forceinline__ bool packed_box(const uint32_t b[3], const float inv[
   float tn[3], tf[3];
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    const half2_t v = __builtin_bit_cast(half2_t, __builtin_amdgcn_alignbit(b[k], b[k], rot[k]));
+    // (line_slabs orients the line along the first axis)
+    const half2_t v = __builtin_bit_cast(half2_t, k == 0 ? b[k] : __builtin_amdgcn_alignbit(b[k], b[k], rot[k]));
     tn[k] = fmaf((float)v.x, inv[k], ox[k]);
     tf[k] = fmaf((float)v.y, inv[k], ox[k]);
   }
@@ -567,38 +587,55 @@ __device__ __forceinline__ uint32_t child_mask(const typename Rec<R, D>::Node& n
   return m;
 }
 
+// Interior record e, by a 32-bit byte offset from the uniform base.  An FP32
+// record is one 64-byte line: four 16-byte loads, kept whole (the compiler
+// would otherwise split them, or fetch entries again in the branches that use
+// them); `meanwhile`, a word on its way from LDS, is waited for with them.
+template <typename R, int D>
+__device__ __forceinline__ typename Rec<R, D>::Node load_node(const typename Rec<R, D>::Node* nodes, int32_t e,
+                                                              int32_t& meanwhile) {
+  using Node = typename Rec<R, D>::Node;
+  if constexpr (sizeof(R) == 4) {
+    const auto* p = (const __attribute__((address_space(1))) char*)nodes + (uint32_t)e * (uint32_t)sizeof(Node);
+    typedef int32_t int4_t __attribute__((ext_vector_type(4)));
+    struct Words { int4_t w[4]; } n;
+    static_assert(sizeof(Words) == sizeof(Node), "one line per record");
+#pragma unroll
+    for (int q = 0; q < 4; ++q) n.w[q] = ((const __attribute__((address_space(1))) int4_t*)p)[q];
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(n.w[0]), "+v"(n.w[1]), "+v"(n.w[2]), "+v"(n.w[3]), "+v"(meanwhile));
+#endif
+    return __builtin_bit_cast(Node, n);
+  } else {
+    return nodes[(uint32_t)e];
+  }
+}
+
 // Calls leaf(first, count) for every leaf whose box the line crosses, depth
-// first with a private stack (one line per thread: the hit-list query).  The
-// path kernel runs the same traversal in its own loop, with the stack in LDS,
-// where lanes park at crossed leaves and test them together.
+// first with a private stack of records (one line per thread: the hit-list
+// query).  The path kernel runs the same traversal in its own loop, with the
+// stack in LDS.
 template <typename R, int D, bool COUNT, typename Leaf>
 __device__ __forceinline__ void for_each_leaf(const SceneView<R, D>& s, const R inv[3], const R ox[3],
                                               const uint32_t rot[3], WorkCount& wc, Leaf&& leaf) {
-  int32_t stk[kMaxDepth];
+  int32_t stk[kMaxDepth + 1];
   int sp = 0;
-  int32_t e = s.root;
-  for (;;) {
-    if (e >= 0) {
-      const typename Rec<R, D>::Node n = s.nodes[e];
-      if (COUNT) wc.nodes += 1;
-      uint32_t m = child_mask<R, D>(n, inv, ox, rot);
-      // continue with the first crossed entry, push the others
-      e = kPop;
+  if (s.root < 0) {  // a tree of one leaf
+    leaf((-1 - s.root) >> 3, ((-1 - s.root) & 7) + 1);
+    return;
+  }
+  stk[sp++] = s.root;
+  while (sp > 0) {
+    const typename Rec<R, D>::Node n = s.nodes[stk[--sp]];
+    if (COUNT) wc.nodes += 1;
+    const uint32_t m = child_mask<R, D>(n, inv, ox, rot);
 #pragma unroll
-      for (int k = 0; k < kArity; ++k) {
-        if (m & (1u << k)) {
-          if (e == kPop) e = n.child[k];
-          else if (sp < kMaxDepth) stk[sp++] = n.child[k];
-        }
+    for (int q = 1; q <= kArity; ++q) {
+      if (m & (1u << (q & (kArity - 1)))) {
+        const int32_t e = n.child[q & (kArity - 1)];
+        if (e < 0) leaf((-1 - e) >> 3, ((-1 - e) & 7) + 1);
+        else if (sp <= kMaxDepth) stk[sp++] = e;
       }
-    } else if (e != kPop) {
-      const int32_t code = -1 - e;
-      leaf(code >> 3, (code & 7) + 1);
-      e = kPop;
-    }
-    if (e == kPop) {
-      if (sp == 0) break;
-      e = stk[--sp];
     }
   }
 }

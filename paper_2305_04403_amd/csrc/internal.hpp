@@ -28,6 +28,7 @@ struct wob_scene_s {
   int32_t guide_shift = 0;
   unsigned long long* d_status = nullptr;  // non-finite path values excluded from solves (sticky)
   double area_total = 0.0;      // |Gamma|
+  int64_t normal_offset = 0;  // within a primitive record, when d_normals is null
   int64_t node_bytes = 0, prim_bytes = 0, device_bytes = 0;
   int32_t n_dirichlet = 0, n_neumann = 0, n_robin = 0;
 };
@@ -63,8 +64,11 @@ template <typename R, int D>
 wob::SceneView<R, D> view(const wob_scene_s* sc) {
   wob::SceneView<R, D> s;
   s.nodes = (const typename wob::Rec<R, D>::Node*)sc->d_nodes;
-  s.prims = (const typename wob::Rec<R, D>::Prim*)sc->d_prims;
-  s.normals = (const R*)sc->d_normals;
+  s.prims = (const char*)sc->d_prims;
+  s.prim_stride = (uint32_t)sc->prim_bytes;
+  // beside the records, or an array of their own
+  s.normals = sc->d_normals ? (const char*)sc->d_normals : (const char*)sc->d_prims + sc->normal_offset;
+  s.normal_stride = sc->d_normals ? (uint32_t)(4 * sizeof(R)) : (uint32_t)sc->prim_bytes;
   s.leaf_of_id = sc->d_leaf_of_id;
   s.area_cdf = sc->d_area_cdf;
   s.area_guide = sc->d_area_guide;

@@ -6,15 +6,27 @@
 
 namespace wob {
 
-// Dynamic LDS of the path kernels: the lanes' traversal stacks and held
-// leaves, stack_cap + kLeafSlots entries of 4 bytes per thread of the block,
-// then one more row (the path counters of the lane groups) and one word (the
-// path offset; sized at launch).
+// Dynamic LDS of the path kernels, in rows of one 4-byte word per thread of the
+// block (consecutive lanes in consecutive banks): kLeafRows rows of held
+// leaves, one row of path counters (of the lane groups), the lanes' traversal
+// stacks of stack_cap + 1 entries, then one word (the path offset; sized at
+// launch).
 extern __shared__ int32_t wob_stack[];
-constexpr int kLeafSlots = 4;
+// A lane parks once it holds kLeafSlots leaves; its last record may have added
+// up to kArity of them.  The wavefront's leaf queue (kQueueRows rows) holds
+// 16-bit entries.
+constexpr int kLeafSlots = 10, kLeafRows = kLeafSlots - 1 + kArity;
+constexpr int kCounterRow = kLeafRows, kHitRow = kCounterRow + 1, kQueueRow = kHitRow + 1;
+constexpr int kQueueRows = 2, kStackRow = kQueueRow + kQueueRows;
+constexpr uint32_t kQueueEntries = kQueueRows * 64 * 2;  // per wavefront
 inline size_t walk_lds_bytes(int stack_cap, int block) {
-  return ((size_t)(stack_cap + kLeafSlots + 1) * (size_t)block + 1) * sizeof(int32_t);
+  return ((size_t)(kStackRow + stack_cap + 1) * (size_t)block + 1) * sizeof(int32_t);
 }
+// The LDS word at an LDS byte address, and wob_stack's address: entries are
+// addressed by one register per lane, with no base to add at each access.
+typedef __attribute__((address_space(3))) int32_t lds_int;
+__device__ __forceinline__ lds_int& lds_word(uint32_t address) { return *(lds_int*)(uintptr_t)address; }
+__device__ __forceinline__ uint32_t lds_base() { return (uint32_t)(uintptr_t)(lds_int*)wob_stack; }
 
 template <typename R, int D>
 struct WalkArgs {
@@ -56,6 +68,35 @@ struct WalkArgs {
   unsigned long long* status;  // solves: count of non-finite path values (excluded from the statistics)
 };
 
+// The walk's arguments, read again from memory from here on: a phase of the
+// walk (a path step, a leaf test, the node loop) loads the few it needs into
+// scalar registers when it begins.  Left to itself the compiler loads all of
+// them once and, as they do not fit the scalar registers, spills them to lanes
+// of vector registers, which it then reads back inside the hot loops.
+template <typename T>
+__device__ __forceinline__ const T& again(const T& a) {
+#ifdef __HIP_DEVICE_COMPILE__
+  typedef const __attribute__((address_space(4))) T* Constant;
+  const uint64_t at = (uint64_t)(uintptr_t)&a;  // the same in every lane
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
+  Constant p = (Constant)(((uint64_t)hi << 32) | lo);
+  asm volatile("" : "+s"(p));
+  return *(const T*)p;
+#else
+  return a;
+#endif
+}
+
+// A uniform value that stays in its scalar register once loaded.
+template <typename T>
+__device__ __forceinline__ T loaded(T v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(v));
+#endif
+  return v;
+}
+
 // One path estimates u_hat(x_0):
 //
 // Double layer (Table 1, Dirichlet; eq. mc_dirichlet_interior_sol and
@@ -77,14 +118,16 @@ struct WalkArgs {
 // sample with probability p_s.  Emission 2 phi s, halved at x_M.
 //
 // A lane runs its paths as a state machine: begin_step draws the vertex's
-// direction (and performs in-plane self-panel steps, which trace nothing)
-// until a line has to be traced; the walk loop (walk_block) steps through the
-// BVH nodes of that line and hands each crossed leaf to leaf_work; end_step
-// consumes the line's hits and calls begin_step for the next vertex.  The
-// lanes of a wavefront therefore trace lines independently instead of every
-// line waiting for the wavefront's longest one.
+// direction (or performs an in-plane self-panel step, which traces nothing);
+// the walk loop (walk_block) steps through the BVH nodes of the line, collecting
+// the leaves it crosses; test_leaves tests the leaves of all lanes of the
+// wavefront; end_step consumes the line's hits.  The lanes of a wavefront
+// therefore trace lines independently instead of every line waiting for the
+// wavefront's longest one.
 
-enum { ST_NONE = 0, ST_LINE = 1, ST_DONE = 2 };
+// A lane's state: no path, a line being traced, a path finished, a vertex whose
+// next step begin_step draws.
+enum { ST_NONE = 0, ST_LINE = 1, ST_DONE = 2, ST_STEP = 3 };
 
 // Extensions of the walk: the corrected walk of the control variate, and the
 // gradient in the evaluation point carried along the same paths.
@@ -133,7 +176,6 @@ struct PathState {
   R d[3], inv[3], ox[3];
   uint32_t rot[3];        // slab-test rotations of packed box words
   HitAcc<R> h;
-  int32_t ni;            // traversal position: an entry, kPop or kDone
   R Wg[3], gacc[3];      // gradient walk: d W / d x0 and the gradient sum
   R Wg0[3];              // gradient walk: the step-0 derivative weight w'
   R acc_main;            // boundary split: the path's value while its coupled walk runs
@@ -305,113 +347,110 @@ template <typename R, int D, int FORM, bool TRACE, bool COUNT, int EXT>
 __device__ __forceinline__ int begin_step(const WalkArgs<R, D>& a, PathState<R, D>& s, WorkCount& wc) {
   constexpr bool CV = ext_kind(EXT) == X_CV, GRAD = ext_kind(EXT) == X_GRAD, VD = ext_vdata(EXT);
   const R phi = a.phi;
-  for (;;) {
-    if (s.i >= a.L) return ST_DONE;
-    s.on_gamma = s.cur_idx >= 0;
-    s.z = (a.problem << 24) | ((uint32_t)s.i << 8);
-    if (s.on_gamma && FORM != F_DL && FORM != F_FWD) {
-      s.gc = load_prim<R, D>(a.scene, s.cur_idx);
-      load_normal<R, D>(a.scene, s.cur_idx, s.nc);
-    }
-    // step 0 from an evaluation point uses the representation formula; in
-    // density mode x0 is itself a vertex of the boundary recursion
-    s.first = FORM != F_FWD && s.i == 0 && !a.density;
-    if constexpr (is_sl(FORM)) {
-      // Table 1: on a Dirichlet part the solution is the given value (tested
-      // here, where the primitive is loaded anyway, rather than in start_path:
-      // a second load there costs the single-layer kernel ~35 registers)
-      if (s.first && s.on_gamma && s.gc.kind == K_DIRICHLET) {
-        const R nz[3] = {0, 0, 0};
-        s.acc = boundary_datum<R, D, VD>(a.prog, s.gc, nz, s.x);
-        return ST_DONE;
-      }
-    }
-    U4 r0;
-    bool have_r0 = false;
-    if constexpr (is_sl(FORM)) {
-      // a Dirichlet vertex (mixed problems): the transformed first-kind row
-      // mu = mu - k int G mu + k u_D, one term at a time (eq.
-      // mixed_second_kind_ish_mc): with probability p_k the next point is
-      // sampled from k G (weight -k G / (p p_k)), otherwise the walk stays at x
-      // (weight 1 / (1 - p_k)); the p_k decision is word 3 of block 0
-      const bool dvert = s.on_gamma && !s.first && s.gc.kind == K_DIRICHLET;
-      s.gscale = s.first ? (R)1 : (R)0;
-      if (dvert) {
-        r0 = philox(s.path, s.point, s.z, 0u, a.k0, a.k1);
-        have_r0 = true;
-        if ((r0.w >> 8) >= a.mixed_thr) {
-          const R ws = (R)1 / ((R)1 - a.mixed_p);
-          s.W *= ws;
-          if (TRACE && s.vp) s.vp[s.i] = -2 - s.gc.id;
-          const R e = sl_emission<R, D, VD>(a, s.gc, s.nc, s.x, s.i + 1 >= a.M);
-          s.acc += s.W * e;
-          if constexpr (GRAD) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-              s.Wg[k] *= ws;
-              s.gacc[k] += s.Wg[k] * e;
-            }
-          }
-          ++s.i;
-          continue;
-        }
-        s.gscale = -a.mixed_k / a.mixed_p;
-      }
-      if constexpr (FORM == F_SL_RIS) {
-        if (!ris_step<R, D, TRACE, GRAD, VD, CV>(a, s)) return ST_DONE;
-        ++s.i;
-        continue;
-      }
-    }
-    if (!have_r0) r0 = philox(s.path, s.point, s.z, 0u, a.k0, a.k1);
-    direction<R, D>(r0.x, r0.y, s.d);
-    bool use_self = false;
-    s.mixture = false;
-    if constexpr (is_sl(FORM)) {
-      s.mixture = s.on_gamma && (s.gscale != (R)0 || s.gc.kind == K_ROBIN);
-      use_self = s.mixture && (r0.z >> 8) < a.self_thr;
-    }
-    if (use_self) {
-      const U4 r1 = philox(s.path, s.point, s.z | 1u, 0u, a.k0, a.k1);
-      R y[3];
-      const R gp = self_panel<R, D>(s.gc, s.nc, s.x, unit<R>(r1.x), unit<R>(r1.y), y);
-      const R w = (s.gscale != (R)0 ? s.gscale * gp : (R)-2 * phi * s.gc.alpha * gp) / a.self_p;
-      if (TRACE && s.vp) s.vp[s.i] = -2 - s.gc.id;
-      s.W *= w;
-      // control variate, line 0: subtract the line-0 table at the own primitive
-      if (CV && s.i == 0 && s.i + 1 < a.M) s.acc -= s.W * a.cv_g0[s.gc.id];
-      s.x[0] = y[0];
-      s.x[1] = y[1];
-      s.x[2] = y[2];
-      // emission at the new vertex (same primitive)
-      const R e = sl_emission<R, D, VD>(a, s.gc, s.nc, s.x, s.i + 1 >= a.M);
-      s.acc += s.W * e;
-      if constexpr (GRAD) {  // a vertex on the boundary: never the first step
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          s.Wg[k] *= w;
-          s.gacc[k] += s.Wg[k] * e;
-        }
-      }
-      ++s.i;
-      continue;
-    }
-    s.last = s.i == a.L - 1;
-    // the direct BIE's last line and the corrected walk's last line need no pick
-    s.select = !((FORM == F_DIRECT || CV) && s.last);
-    s.sum = CV && (s.i > 0 || s.last);
-    line_slabs<R, D>(a.scene, s.x, s.d, s.inv, s.ox, s.rot);
-    s.h.m = 0;
-    s.h.key = 0xffffffffu;
-    s.h.id = 0x7fffffff;
-    s.h.idx = -1;
-    s.h.t = 0;
-    s.h.src = 0;
-    if constexpr (GRAD) s.h.srcg[0] = s.h.srcg[1] = s.h.srcg[2] = 0;
-    s.ni = a.scene.root;
-    if (COUNT) wc.lines += 1;
-    return ST_LINE;
+  if (s.i >= a.L) return ST_DONE;
+  s.on_gamma = s.cur_idx >= 0;
+  s.z = (a.problem << 24) | ((uint32_t)s.i << 8);
+  if (s.on_gamma && FORM != F_DL && FORM != F_FWD) {
+    s.gc = load_prim<R, D>(a.scene, s.cur_idx);
+    load_normal<R, D>(a.scene, s.cur_idx, s.nc);
   }
+  // step 0 from an evaluation point uses the representation formula; in
+  // density mode x0 is itself a vertex of the boundary recursion
+  s.first = FORM != F_FWD && s.i == 0 && !a.density;
+  if constexpr (is_sl(FORM)) {
+    // Table 1: on a Dirichlet part the solution is the given value (tested
+    // here, where the primitive is loaded anyway, rather than in start_path:
+    // a second load there costs the single-layer kernel ~35 registers)
+    if (s.first && s.on_gamma && s.gc.kind == K_DIRICHLET) {
+      const R nz[3] = {0, 0, 0};
+      s.acc = boundary_datum<R, D, VD>(a.prog, s.gc, nz, s.x);
+      return ST_DONE;
+    }
+  }
+  U4 r0;
+  bool have_r0 = false;
+  if constexpr (is_sl(FORM)) {
+    // a Dirichlet vertex (mixed problems): the transformed first-kind row
+    // mu = mu - k int G mu + k u_D, one term at a time (eq.
+    // mixed_second_kind_ish_mc): with probability p_k the next point is
+    // sampled from k G (weight -k G / (p p_k)), otherwise the walk stays at x
+    // (weight 1 / (1 - p_k)); the p_k decision is word 3 of block 0
+    const bool dvert = s.on_gamma && !s.first && s.gc.kind == K_DIRICHLET;
+    s.gscale = s.first ? (R)1 : (R)0;
+    if (dvert) {
+      r0 = philox(s.path, s.point, s.z, 0u, a.k0, a.k1);
+      have_r0 = true;
+      if ((r0.w >> 8) >= a.mixed_thr) {
+        const R ws = (R)1 / ((R)1 - a.mixed_p);
+        s.W *= ws;
+        if (TRACE && s.vp) s.vp[s.i] = -2 - s.gc.id;
+        const R e = sl_emission<R, D, VD>(a, s.gc, s.nc, s.x, s.i + 1 >= a.M);
+        s.acc += s.W * e;
+        if constexpr (GRAD) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            s.Wg[k] *= ws;
+            s.gacc[k] += s.Wg[k] * e;
+          }
+        }
+        ++s.i;
+        return ST_STEP;
+      }
+      s.gscale = -a.mixed_k / a.mixed_p;
+    }
+    if constexpr (FORM == F_SL_RIS) {
+      if (!ris_step<R, D, TRACE, GRAD, VD, CV>(a, s)) return ST_DONE;
+      ++s.i;
+      return ST_STEP;
+    }
+  }
+  if (!have_r0) r0 = philox(s.path, s.point, s.z, 0u, a.k0, a.k1);
+  direction<R, D>(r0.x, r0.y, s.d);
+  bool use_self = false;
+  s.mixture = false;
+  if constexpr (is_sl(FORM)) {
+    s.mixture = s.on_gamma && (s.gscale != (R)0 || s.gc.kind == K_ROBIN);
+    use_self = s.mixture && (r0.z >> 8) < a.self_thr;
+  }
+  if (use_self) {
+    const U4 r1 = philox(s.path, s.point, s.z | 1u, 0u, a.k0, a.k1);
+    R y[3];
+    const R gp = self_panel<R, D>(s.gc, s.nc, s.x, unit<R>(r1.x), unit<R>(r1.y), y);
+    const R w = (s.gscale != (R)0 ? s.gscale * gp : (R)-2 * phi * s.gc.alpha * gp) / a.self_p;
+    if (TRACE && s.vp) s.vp[s.i] = -2 - s.gc.id;
+    s.W *= w;
+    // control variate, line 0: subtract the line-0 table at the own primitive
+    if (CV && s.i == 0 && s.i + 1 < a.M) s.acc -= s.W * a.cv_g0[s.gc.id];
+    s.x[0] = y[0];
+    s.x[1] = y[1];
+    s.x[2] = y[2];
+    // emission at the new vertex (same primitive)
+    const R e = sl_emission<R, D, VD>(a, s.gc, s.nc, s.x, s.i + 1 >= a.M);
+    s.acc += s.W * e;
+    if constexpr (GRAD) {  // a vertex on the boundary: never the first step
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        s.Wg[k] *= w;
+        s.gacc[k] += s.Wg[k] * e;
+      }
+    }
+    ++s.i;
+    return ST_STEP;
+  }
+  s.last = s.i == a.L - 1;
+  // the direct BIE's last line and the corrected walk's last line need no pick
+  s.select = !((FORM == F_DIRECT || CV) && s.last);
+  s.sum = CV && (s.i > 0 || s.last);
+  line_slabs<R, D>(a.scene, s.x, s.d, s.inv, s.ox, s.rot);
+  s.h.m = 0;
+  s.h.key = 0xffffffffu;
+  s.h.id = 0x7fffffff;
+  s.h.idx = -1;
+  s.h.t = 0;
+  s.h.src = 0;
+  if constexpr (GRAD && FORM == F_DIRECT) s.h.srcg[0] = s.h.srcg[1] = s.h.srcg[2] = 0;
+  if (COUNT) wc.lines += 1;
+  return ST_LINE;
 }
 
 // couple >= 0 (gradient walks of the double layer): instead of path `path`'s
@@ -420,9 +459,10 @@ __device__ __forceinline__ int begin_step(const WalkArgs<R, D>& a, PathState<R, 
 // kept aside.  Both starts end in the same begin_step call, so that its code
 // is inlined once.
 template <typename R, int D, int FORM, bool TRACE, bool COUNT, int EXT>
-__device__ __forceinline__ int start_path(const WalkArgs<R, D>& a, PathState<R, D>& s, uint32_t path,
+__device__ __forceinline__ int start_path(const WalkArgs<R, D>& a0, PathState<R, D>& s, uint32_t path,
                                           int64_t item, WorkCount& wc, int32_t couple = -1,
                                           int64_t point = 0) {
+  const WalkArgs<R, D>& a = again(a0);
   constexpr bool GRAD = ext_kind(EXT) == X_GRAD, VD = ext_vdata(EXT);
   s.path = path;
   bool coupled_start = false;
@@ -433,6 +473,7 @@ __device__ __forceinline__ int start_path(const WalkArgs<R, D>& a, PathState<R, 
     s.coupled = true;
     if (couple >= a.scene.n_prims) {  // a caller error: the gradient is NaN
       s.acc = (R)NAN;
+      asm volatile("");  // else merged with other stores, and the state moved to scratch
       return ST_DONE;
     }
     if (TRACE) s.vp = s.vm = nullptr;
@@ -452,7 +493,8 @@ __device__ __forceinline__ int start_path(const WalkArgs<R, D>& a, PathState<R, 
   } else {
     if constexpr (GRAD) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) s.Wg0[k] = 0;
+      for (int k = 0; k < 3; ++k)
+        if constexpr (FORM == F_DL) s.Wg0[k] = 0;
       s.coupled = false;
     }
     if constexpr (FORM == F_FWD) {
@@ -495,7 +537,7 @@ __device__ __forceinline__ int start_path(const WalkArgs<R, D>& a, PathState<R, 
       s.i = 0;
       s.cur_idx = leaf;
       fwd_record<R, D>(a, s, 0, g.id, 0);
-      return begin_step<R, D, FORM, TRACE, COUNT, EXT>(a, s, wc);
+      return ST_STEP;
     }
     if (TRACE) {
       s.vp = a.vtx_prim ? a.vtx_prim + item * a.L : nullptr;
@@ -509,6 +551,7 @@ __device__ __forceinline__ int start_path(const WalkArgs<R, D>& a, PathState<R, 
     // so is a density-mode point off the boundary (it has no boundary unknown)
     if (s.prim0 < -1 || s.prim0 >= a.scene.n_prims || (a.density && s.prim0 < 0)) {
       s.acc = (R)NAN;
+      asm volatile("");  // else merged with other stores, and the state moved to scratch
       return ST_DONE;
     }
     s.cur_idx = s.prim0 >= 0 ? a.scene.leaf_of_id[s.prim0] : -1;
@@ -530,57 +573,115 @@ __device__ __forceinline__ int start_path(const WalkArgs<R, D>& a, PathState<R, 
       for (int k = 0; k < 3; ++k) s.Wg[k] = s.gacc[k] = 0;
     }
   }
-  return begin_step<R, D, FORM, TRACE, COUNT, EXT>(a, s, wc);
+  return ST_STEP;
 }
 
 
-// The primitives of the crossed leaves a lane holds (one to four) on the
-// current line.  The primitive loop
-// only tests and records the accepted primitives in a bit mask; the hits are
-// then handled in a loop of their own, so that the lanes with a hit in this
-// leaf phase do that work together instead of one or two at a time inside the
-// primitive loop.  Per hit: count it; with `select`, draw its key (Philox
-// block 2, w = caller id) and keep the smallest (key, id) -- the line
-// parameter and barycentrics of the kept hit are computed once, in end_step;
-// for the direct BIE add G q / p_all to the source sum; for the corrected walk
-// add a(h) F(y_h).
-template <typename R, int D, int FORM, bool COUNT, int EXT>
-__device__ __forceinline__ void leaf_work(const WalkArgs<R, D>& a, PathState<R, D>& s, int32_t code,
-                                          int32_t code2, int32_t code3, int32_t code4, WorkCount& wc) {
-  static_assert(kLeafSlots == 4, "leaf_work takes four leaf codes");
+// v of the lane whose number times four is lane4 (every lane takes part).
+template <typename T>
+__device__ __forceinline__ T of_lane(T v, uint32_t lane4) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_ds_bpermute((int)lane4, __builtin_bit_cast(int, v)));
+  } else {
+    struct W { int w[2]; } u = __builtin_bit_cast(W, v);
+    u.w[0] = __builtin_amdgcn_ds_bpermute((int)lane4, u.w[0]);
+    u.w[1] = __builtin_amdgcn_ds_bpermute((int)lane4, u.w[1]);
+    return __builtin_bit_cast(T, u);
+  }
+}
+
+static_assert(kLeafPrims == 2 && 2 * kLeafRows <= 32, "test_leaves: two bits per leaf slot");
+// Tests the leaves that the lanes of the wavefront hold (a lane's are the words
+// from its address lbase up to lo, a row apart).  The leaves of all lanes are
+// queued and dealt out, one per lane and pass, whichever lane holds them: a
+// lane fetches the line of its leaf's owner, tests the leaf's primitives (at
+// most kLeafPrims, their records loaded together) and notes the accepted ones in
+// the owner's word.  Tested by their owners, the leaves of a wavefront took as
+// many passes as the busiest lane has primitives (about eight, a third of the
+// lanes at work), each waiting for its record; dealt out, two or three passes.
+// Returns the lane's own hits: bit 2 s + b for primitive b of the leaf
+// in slot s.  Every lane of the wavefront calls it.
+template <typename R, int D, bool COUNT, int BLOCK>
+__device__ __forceinline__ uint32_t test_leaves(const WalkArgs<R, D>& a0, const PathState<R, D>& s, uint32_t lbase,
+                                                uint32_t lo, WorkCount& wc) {
+  constexpr uint32_t kRow = BLOCK * sizeof(int32_t);
+  typedef __attribute__((address_space(3))) uint16_t lds_u16;
+  const uint32_t lane = threadIdx.x & 63u, wave0 = lbase - lane * 4u;  // the wavefront's first word of the row
+  const uint32_t queue = wave0 - (threadIdx.x - lane) * 4u + kQueueRow * kRow +
+                         (threadIdx.x >> 6) * (kQueueEntries * 2u);
+  if (__ballot(lbase < lo) == 0) return 0;
+  lds_word(lbase + kHitRow * kRow) = 0;
+  const char* const prims = loaded(again(a0).scene.prims);
+  const uint32_t stride = loaded(again(a0).scene.prim_stride);
+  uint32_t at_slot = lbase;
+  for (bool more = true; more;) {
+    // slot by slot, as many as the queue holds
+    uint32_t total = 0;
+    for (;; at_slot += kRow) {
+      const uint64_t held = __ballot(at_slot < lo);
+      more = held != 0;
+      if (!more || total + __popcll(held) > kQueueEntries) break;
+      if (at_slot < lo) {
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(held >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)held, 0u));
+        *(lds_u16*)(uintptr_t)(queue + 2u * (total + rank)) = (uint16_t)(at_slot - wave0);
+      }
+      total += __popcll(held);
+    }
+    for (uint32_t i = 0; i < total; i += 64) {
+      const bool mine = i + lane < total;
+      const uint32_t at = mine ? *(lds_u16*)(uintptr_t)(queue + 2u * (i + lane)) : 0u;
+      const uint32_t owner4 = at & 255u;
+      R x[3], d[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        x[k] = k < D ? of_lane(s.x[k], owner4) : (R)0;
+        d[k] = k < D ? of_lane(s.d[k], owner4) : (R)0;
+      }
+      const int32_t own = of_lane(s.cur_idx, owner4);
+      if (mine) {
+        const int32_t code = -1 - lds_word(wave0 + at), first = code >> 3;
+        const bool two = (code & 7) != 0;
+        const PrimGeo<R> g0 = load_prim<R, D>(prims, stride, first),
+                         g1 = load_prim<R, D>(prims, stride, first + (two ? 1 : 0));
+        R t, u, v;
+        uint32_t hit = hit_prim<R, D>(g0, x, d, t, u, v) && first != own ? 1u : 0u;
+        if (two && hit_prim<R, D>(g1, x, d, t, u, v) && first + 1 != own) hit |= 2u;
+        if (COUNT) wc.prims += (first != own ? 1 : 0) + (two && first + 1 != own ? 1 : 0);
+        if (hit != 0)
+          __hip_atomic_fetch_or((int32_t*)&lds_word(wave0 + kHitRow * kRow + owner4),
+                                (int32_t)(hit << (2u * (at / kRow))), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      }
+    }
+  }
+  return (uint32_t)lds_word(lbase + kHitRow * kRow);
+}
+
+// The hits of a lane's line among the leaves it held.  Per hit: count it; with
+// `select`, draw its key (Philox block 2, w = caller id) and keep the smallest
+// (key, id) -- the line parameter and barycentrics of the kept hit are computed
+// once, in end_step; for the direct BIE add G q / p_all to the source sum; for
+// the corrected walk add a(h) F(y_h).
+template <typename R, int D, int FORM, bool COUNT, int EXT, int BLOCK>
+__device__ __forceinline__ void leaf_hits(const WalkArgs<R, D>& a0, PathState<R, D>& s, uint32_t accepted,
+                                          uint32_t lbase, WorkCount& wc) {
+  const WalkArgs<R, D>& a = again(a0);
   constexpr bool CV = ext_kind(EXT) == X_CV, GRAD = ext_kind(EXT) == X_GRAD, VD = ext_vdata(EXT);
   const SceneView<R, D>& sc = a.scene;
   {
-    // one to four leaves (codes -1 = none after the first): primitive b of the
-    // row is first + b (b < count), then the second leaf's, and so on
-    const int32_t first = code >> 3, count = (code & 7) + 1;
-    const int32_t c2 = code2 >= 0 ? (code2 & 7) + 1 : 0, c3 = code3 >= 0 ? (code3 & 7) + 1 : 0;
-    const int32_t first2 = (code2 >> 3) - count, first3 = (code3 >> 3) - count - c2;
-    const int32_t first4 = (code4 >> 3) - count - c2 - c3;
-    const int32_t total = count + c2 + c3 + (code4 >= 0 ? (code4 & 7) + 1 : 0);
     constexpr bool GEO = FORM == F_DIRECT || CV;  // per-hit work needs the hit's geometry
-    uint32_t accepted = 0;  // bit b: primitive b of the leaves is hit
-    int32_t id0 = 0;        // caller id of the first hit (no reload for it)
-    for (int32_t b = 0; b < total; ++b) {
-      const int32_t j = (b < count ? first : (b < count + c2 ? first2 : (b < count + c2 + c3 ? first3 : first4))) + b;
-      if (j == s.cur_idx) continue;
-      if (COUNT) wc.prims += 1;
-      const PrimGeo<R> g = load_prim<R, D>(sc, j);
-      R t, u, v;
-      if (hit_prim<R, D>(g, s.x, s.d, t, u, v)) {
-        if (!accepted) id0 = g.id;
-        accepted |= 1u << b;
-      }
-    }
-    bool later = false;
     while (accepted) {
       const int32_t b = __builtin_ctz(accepted);
-      const int32_t j = (b < count ? first : (b < count + c2 ? first2 : (b < count + c2 + c3 ? first3 : first4))) + b;
       accepted &= accepted - 1;
+      const int32_t j = ((-1 - lds_word(lbase + (b >> 1) * (BLOCK * sizeof(int32_t)))) >> 3) + (b & 1);
       PrimGeo<R> g;
-      if (GEO || later) g = load_prim<R, D>(sc, j);
-      const int32_t id = (GEO || later) ? g.id : id0;
-      later = true;
+      int32_t id;
+      if constexpr (GEO) {
+        g = load_prim<R, D>(sc, j);
+        id = g.id;
+      } else {
+        id = prim_record<R, D>(sc.prims, sc.prim_stride, j).idkind & kIdMask;
+      }
       if (COUNT) wc.hits += 1;
       s.h.m += 1;
       if (s.select) {
@@ -635,7 +736,8 @@ __device__ __forceinline__ void leaf_work(const WalkArgs<R, D>& a, PathState<R, 
 }
 
 template <typename R, int D, int FORM, bool TRACE, bool COUNT, int EXT>
-__device__ __forceinline__ int end_step(const WalkArgs<R, D>& a, PathState<R, D>& s, WorkCount& wc) {
+__device__ __forceinline__ int end_step(const WalkArgs<R, D>& a0, PathState<R, D>& s, WorkCount& wc) {
+  const WalkArgs<R, D>& a = again(a0);
   constexpr bool CV = ext_kind(EXT) == X_CV, GRAD = ext_kind(EXT) == X_GRAD, VD = ext_vdata(EXT);
   const R phi = a.phi;
   HitAcc<R>& h = s.h;
@@ -724,7 +826,7 @@ __device__ __forceinline__ int end_step(const WalkArgs<R, D>& a, PathState<R, D>
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         s.Wg[k] = s.Wg[k] * w + s.W * wg[k];
-        s.Wg0[k] = wg[k];
+        if constexpr (FORM == F_DL) s.Wg0[k] = wg[k];
       }
     } else {
 #pragma unroll
@@ -763,7 +865,7 @@ __device__ __forceinline__ int end_step(const WalkArgs<R, D>& a, PathState<R, D>
     fwd_record<R, D>(a, s, s.i + 1, gy.id, h.m);
   }
   ++s.i;
-  return begin_step<R, D, FORM, TRACE, COUNT, EXT>(a, s, wc);
+  return ST_STEP;
 }
 
 
@@ -821,17 +923,17 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
   const int64_t point0 =
       block_index * (BLOCK >> a.lpp_shift) + (POOL ? ((tid >> a.lpp_shift) & ~1) : (tid >> a.lpp_shift));
   const int lane_in_point = tid & (lpp - 1);
-  // the group's next free counter, in LDS after the stacks and held leaves
+  // the group's next free counter, in LDS after the held leaves
   // (the first G counters start at once); only this wavefront reads and
   // writes it
   if ((tid & (G - 1)) == 0)
-    __hip_atomic_store(wob_stack + (a.scene.stack_cap + kLeafSlots) * BLOCK + tid, G, __ATOMIC_RELAXED,
+    __hip_atomic_store(wob_stack + kCounterRow * BLOCK + tid, G, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_WAVEFRONT);
   // the path offset, read back at each path's start: kept in LDS rather than
   // in a scalar register across the loops (the kernel's scalar registers are
   // all in use; one more spills others into the hot loops).  Every wavefront
   // writes the same value before it reads it.
-  int32_t* const offset_word = wob_stack + (a.scene.stack_cap + kLeafSlots + 1) * BLOCK;
+  int32_t* const offset_word = wob_stack + (kStackRow + a.scene.stack_cap + 1) * BLOCK;
   if ((tid & 63) == 0) *offset_word = a.path_offset;
   // counter c of the group -> the path's point (0 or 1 within the pool) and
   // index; false past the group's last path (c is taken in increasing order,
@@ -862,9 +964,9 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
   {
     // The lane's paths (first the one of counter c = its place in the group,
     // then the group's next free ones) run as one state machine.  Lanes step
-    // through BVH nodes; a lane that has reached four crossed leaves parks
-    // until half of the stepping lanes have parked, and the lanes holding
-    // leaves then test them together; a lane at the end of its line parks
+    // through BVH nodes; a lane that holds kLeafSlots crossed leaves parks
+    // until half of the stepping lanes have parked, and the wavefront then
+    // tests the leaves of all its lanes; a lane at the end of its line parks
     // until a quarter of the working lanes have, and those lanes then take
     // their path steps together.  That code thus runs on many lanes at
     // once instead of on the one or two lanes that stand at a leaf or a line
@@ -873,14 +975,28 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
     int k = 0, pl = 0;
     int64_t point = point0;  // the point of the lane's path
     int st = ST_NONE;
-    // the lane's traversal stack: LDS, entry k at wob_stack[k * BLOCK + tid]
-    // (consecutive lanes in consecutive banks); empty between lines.  After
-    // its stack_cap entries come kLeafSlots more: the crossed leaves the lane
-    // holds (nq of them) until the leaf test; a lane holding fewer than
-    // kLeafSlots keeps stepping
-    int32_t* const stk = wob_stack + tid;
-    int32_t* const leafq = stk + a.scene.stack_cap * BLOCK;
-    int sp = 0, nq = 0;
+    // the lane's traversal stack and the crossed leaves it holds until the
+    // leaf test: the top entry in a register (kEnd when the stack is empty,
+    // which ends the line), the entries below it in LDS over a kEnd at the
+    // bottom, `so` the LDS address of the next free one; `lo` the next free
+    // leaf slot (lbase when it holds none); a lane holding fewer than
+    // kLeafSlots leaves keeps stepping
+    constexpr uint32_t kRow = BLOCK * sizeof(int32_t);
+    const uint32_t lbase = lds_base() + (uint32_t)tid * sizeof(int32_t), sbase = lbase + kStackRow * kRow;
+    uint32_t so = sbase + kRow, lo = lbase;
+    int32_t top = kEnd;
+    lds_word(sbase) = kEnd;
+    // a line starts with the root on its lane's stack
+    auto begin_line = [&]() {
+      if (st == ST_LINE) {
+        const int32_t root = again(a).scene.root;
+        const bool leaf = root < 0;  // a tree of one leaf
+        so = sbase + kRow;
+        top = leaf ? kEnd : root;
+        lo = leaf ? lbase + kRow : lbase;
+        if (leaf) lds_word(lbase) = root;
+      }
+    };
     auto load_point = [&]() {
       if constexpr (FORM == F_FWD) {
         s.point = 0xfffffffeu;  // forward paths: no evaluation point
@@ -899,152 +1015,157 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
                                                       wc);
     }
     for (;;) {
-      // finished paths: record, start the lane's next one
-      while (st == ST_DONE) {
-        // boundary split (gradient walks of the double layer): a path whose
-        // point has an anchor and whose line 0 met the boundary runs the
-        // coupled walk from the anchor next, then subtracts w' times its value
-        int32_t couple = -1;
-        bool take = false;
-        {
-          if constexpr (GRAD && FORM == F_DL) {
-            if (s.coupled) {
+      const int idle = __popcll(__ballot(st == ST_NONE));
+      if (idle == 64) break;
+      // the path steps run together, once a quarter of the working lanes wait
+      // for one (1/8, 1/4, 3/8: 334.1, 330.6, 329.1 ms on the three-tori
+      // workload, 6.47, 6.39, 6.46 ms on the exterior Neumann one): lanes at the end of their line
+      // take its hits, lanes whose path ended record it and take the next one,
+      // and all of them then begin their next line (in one place for new and
+      // for continuing paths; an in-plane step, which traces no line, waits for
+      // the next time)
+      const bool at_end = st == ST_LINE && top == kEnd && lo == lbase;
+      const int waiting = __popcll(__ballot(at_end || st == ST_STEP || st == ST_DONE));
+      if (4 * waiting >= 64 - idle) {
+        if (at_end) st = end_step<R, D, FORM, TRACE, COUNT, KEXT>(a, s, wc);
+        // finished paths: record, start the lane's next one
+        if (st == ST_DONE) {
+          // boundary split (gradient walks of the double layer): a path whose
+          // point has an anchor and whose line 0 met the boundary runs the
+          // coupled walk from the anchor next, then subtracts w' times its value
+          int32_t couple = -1;
+          bool take = false;
+          {
+            if constexpr (GRAD && FORM == F_DL) {
+              if (s.coupled) {
 #pragma unroll
-              for (int c = 0; c < 3; ++c) s.gacc[c] -= s.Wg0[c] * s.acc;
-              s.acc = s.acc_main;
-              s.coupled = false;
-            } else if (a.anchor_prim) {
-              const int32_t anchor = a.anchor_prim[point];
-              if (anchor >= 0 && (s.Wg0[0] != (R)0 || s.Wg0[1] != (R)0 || s.Wg0[2] != (R)0)) couple = anchor;
-              else if (anchor < -1) s.gacc[0] = (R)NAN;  // a caller error: the gradient is NaN
-            }
-          }
-          if (couple < 0) {
-            const R v = s.acc;
-            if (TRACE) a.path_out[point * (int64_t)a.N + k] = v;
-            bool finite = isfinite(v);
-            if constexpr (GRAD) {
-#pragma unroll
-              for (int c = 0; c < GD; ++c) {
-                if (TRACE) a.path_grad_out[(point * (int64_t)a.N + k) * D + c] = s.gacc[c];
-                finite = finite && isfinite(s.gacc[c]);
+                for (int c = 0; c < 3; ++c) s.gacc[c] -= s.Wg0[c] * s.acc;
+                s.acc = s.acc_main;
+                s.coupled = false;
+              } else if (a.anchor_prim) {
+                const int32_t anchor = a.anchor_prim[point];
+                if (anchor >= 0 && (s.Wg0[0] != (R)0 || s.Wg0[1] != (R)0 || s.Wg0[2] != (R)0)) couple = anchor;
+                else if (anchor < -1) s.gacc[0] = (R)NAN;  // a caller error: the gradient is NaN
               }
             }
-            if (POOL && finite && pl) {
-              n1 += 1.0;
-              const double dv = (double)v - mean1;
-              mean1 += dv / n1;
-              m21 += dv * ((double)v - mean1);
-            } else if (finite) {
-              n += 1.0;
-              const double dv = (double)v - mean;
-              mean += dv / n;
-              m2 += dv * ((double)v - mean);
+            if (couple < 0) {
+              const R v = s.acc;
+              if (TRACE) a.path_out[point * (int64_t)a.N + k] = v;
+              bool finite = isfinite(v);
               if constexpr (GRAD) {
 #pragma unroll
                 for (int c = 0; c < GD; ++c) {
-                  const double dg = (double)s.gacc[c] - gmean[c];
-                  gmean[c] += dg / n;
-                  gm2[c] += dg * ((double)s.gacc[c] - gmean[c]);
+                  if (TRACE) a.path_grad_out[(point * (int64_t)a.N + k) * D + c] = s.gacc[c];
+                  finite = finite && isfinite(s.gacc[c]);
                 }
               }
-            } else if (!TRACE && !COUNT && FORM != F_FWD && a.status) {
-              // a non-finite path (degenerate geometry, an invalid primitive id, data
-              // singular on the boundary) is counted and left out of the statistics
-              atomicAdd(a.status, 1ull);
+              if (POOL && finite && pl) {
+                n1 += 1.0;
+                const double dv = (double)v - mean1;
+                mean1 += dv / n1;
+                m21 += dv * ((double)v - mean1);
+              } else if (finite) {
+                n += 1.0;
+                const double dv = (double)v - mean;
+                mean += dv / n;
+                m2 += dv * ((double)v - mean);
+                if constexpr (GRAD) {
+#pragma unroll
+                  for (int c = 0; c < GD; ++c) {
+                    const double dg = (double)s.gacc[c] - gmean[c];
+                    gmean[c] += dg / n;
+                    gm2[c] += dg * ((double)s.gacc[c] - gmean[c]);
+                  }
+                }
+              } else if (!TRACE && !COUNT && FORM != F_FWD && a.status) {
+                // a non-finite path (degenerate geometry, an invalid primitive id, data
+                // singular on the boundary) is counted and left out of the statistics
+                atomicAdd(a.status, 1ull);
+              }
+              take = true;
             }
-            take = true;
           }
-        }
-        // the lanes of the group that take a path here get its next counters in
-        // lane order (every lane reads the counter before the first one of
-        // them writes it back)
-        const uint64_t grab = __ballot(take);
-        bool go = couple >= 0;
-        if (take) {
-          const int lane = tid & 63;
-          const uint64_t mine = G == 64 ? grab : grab & (((1ull << G) - 1) << (lane & ~(G - 1)));
-          const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32),
-                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
-          // atomic loads and stores: other lanes write the counter, and a plain
-          // load may be hoisted out of this loop and kept in a register that
-          // only the writing lane updates (stale counters, repeated paths)
-          int32_t* const gnext = wob_stack + (a.scene.stack_cap + kLeafSlots) * BLOCK + (tid & ~(G - 1));
-          const int c = __hip_atomic_load(gnext, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + rank;
-          if (rank == 0) __hip_atomic_store(gnext, c + __popcll(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-          int pn;
-          go = path_of(c, pn, k);
-          if (POOL && go && pn != pl) {  // the pool's second point: its data
-            pl = pn;
-            point = point0 + pl;
-            load_point();
+          // the lanes of the group that take a path here get its next counters in
+          // lane order (every lane reads the counter before the first one of
+          // them writes it back)
+          const uint64_t grab = __ballot(take);
+          bool go = couple >= 0;
+          if (take) {
+            const int lane = tid & 63;
+            const uint64_t mine = G == 64 ? grab : grab & (((1ull << G) - 1) << (lane & ~(G - 1)));
+            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+            // atomic loads and stores: other lanes write the counter, and a plain
+            // load may be hoisted out of this loop and kept in a register that
+            // only the writing lane updates (stale counters, repeated paths)
+            int32_t* const gnext = wob_stack + kCounterRow * BLOCK + (tid & ~(G - 1));
+            const int c = __hip_atomic_load(gnext, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + rank;
+            if (rank == 0) __hip_atomic_store(gnext, c + __popcll(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            int pn;
+            go = path_of(c, pn, k);
+            if (POOL && go && pn != pl) {  // the pool's second point: its data
+              pl = pn;
+              point = point0 + pl;
+              load_point();
+            }
           }
+          st = go ? start_path<R, D, FORM, TRACE, COUNT, KEXT>(a, s, (uint32_t)(*offset_word + k),
+                                                               point * (int64_t)a.N + k, wc,
+                                                               couple, point)
+                  : ST_NONE;
         }
-        st = go ? start_path<R, D, FORM, TRACE, COUNT, KEXT>(a, s, (uint32_t)(*offset_word + k),
-                                                             point * (int64_t)a.N + k, wc,
-                                                             couple, point)
-                : ST_NONE;
+        if (st == ST_STEP) {
+          st = begin_step<R, D, FORM, TRACE, COUNT, KEXT>(again(a), s, wc);
+          begin_line();
+        }
       }
-      const int idle = __popcll(__ballot(st == ST_NONE));
-      if (idle == 64) break;
-      // lanes parked at the end of their line, and lanes that step through nodes
-      const int ends = __popcll(__ballot(st == ST_LINE && nq == 0 && s.ni == kDone));
-      const int active = 64 - idle - ends;
-      // node steps until half of the stepping lanes hold four crossed leaves
-      // or stand at the end of their line; a lane keeps stepping while it
-      // holds fewer (measured on the icosphere benchmark: parking at the
-      // first / second / third / fourth leaf 622 / 694 / 725 / 733 M path
-      // samples/s; with two, a wait for 3/8, 1/2, 5/8 of the lanes: 678, 688,
-      // 677; with four and the shared paths, 3/8, 1/2, 5/8 on the three-tori
-      // workload: 1,284, 1,303, 1,287)
-      const int want = (active * 4 + 7) >> 3;
-      bool trav = st == ST_LINE && nq == 0 && s.ni != kDone;
+      if constexpr (FORM == F_SL_RIS) continue;  // no lines
+      // lanes that step through nodes
+      const int active = __popcll(__ballot(st == ST_LINE && (top != kEnd || lo != lbase)));
+      // node steps until half of the stepping lanes hold kLeafSlots crossed
+      // leaves or stand at the end of their line; a lane keeps stepping while
+      // it holds fewer.  Slots of 4 / 6 / 8 / 10: three-tori workload 330.6 /
+      // 327.3 / 325.8 / 323 ms, exterior Neumann on 62,720 triangles 6.39 / 6.13
+      // / 6.01 / 5.95 ms (more leaves in hand fill the passes of test_leaves;
+      // the LDS of 13 costs more than it gives); a wait for 3/8, 1/2, 5/8 of
+      // the lanes: 329.1, 330.6, 332.5 and 6.41, 6.39, 6.51 ms (four slots)
+      const int want = (active + 1) >> 1;
+      bool trav = st == ST_LINE && top != kEnd;
+      const typename Rec<R, D>::Node* const nodes = loaded(again(a).scene.nodes);
       while (trav) {
         if (active - __popcll(__ballot(1)) >= want) break;
-        // one step: take the position (or pop it), fetch an interior record by
-        // a 32-bit byte offset from the uniform base, test its child boxes,
-        // continue with one crossed entry and push the others; a leaf entry
-        // goes to the lane's leaf queue, and the fourth one parks the lane
-        int32_t e = s.ni;
-        if (e == kPop) e = sp > 0 ? stk[--sp * BLOCK] : kDone;
-        if (e >= 0 && e != kDone) {
-          using Node = typename Rec<R, D>::Node;
-          const Node node = *reinterpret_cast<const Node*>(reinterpret_cast<const char*>(a.scene.nodes) +
-                                                           (uint32_t)e * (uint32_t)sizeof(Node));
-          if (COUNT) wc.nodes += 1;
-          const uint32_t m = child_mask<R, D>(node, s.inv, s.ox, s.rot);
-          // continue with the first crossed entry, push the others
-          e = kPop;
+        // one step: take the top entry (its successor comes from LDS while the
+        // record is fetched) and test its child boxes; crossed leaves go to the
+        // lane's leaf slots, crossed records on the stack, the first one last,
+        // so that it is taken next
+        const int32_t e = top;
+        so -= kRow;
+        top = lds_word(so);
+        const typename Rec<R, D>::Node node = load_node<R, D>(nodes, e, top);
+        if (COUNT) wc.nodes += 1;
+        const uint32_t m = child_mask<R, D>(node, s.inv, s.ox, s.rot);
 #pragma unroll
-          for (int q = 0; q < kArity; ++q) {
-            if (m & (1u << q)) {
-              if (e == kPop) e = node.child[q];
-              else if (sp < a.scene.stack_cap) stk[sp++ * BLOCK] = node.child[q];
+        for (int q = 1; q <= kArity; ++q) {
+          if (m & (1u << (q & (kArity - 1)))) {
+            const int32_t c = node.child[q & (kArity - 1)];
+            if (c < 0) {
+              lds_word(lo) = c;
+              lo += kRow;
+              asm volatile("");  // not to be merged with the push
+            } else {
+              lds_word(so) = top;
+              so += kRow;
+              top = c;
             }
           }
         }
-        const bool at_leaf = e < 0 && e != kPop;
-        if (at_leaf) leafq[nq++ * BLOCK] = -1 - e;
-        s.ni = at_leaf ? kPop : e;
-        trav = nq < kLeafSlots && e != kDone;
+        trav = lo < lbase + kLeafSlots * kRow && top != kEnd;
       }
-      // the lanes holding leaves test them together
-      if (nq > 0) {
-        const int32_t c1 = leafq[0], c2 = nq > 1 ? leafq[BLOCK] : -1, c3 = nq > 2 ? leafq[2 * BLOCK] : -1;
-        const int32_t c4 = nq > 3 ? leafq[3 * BLOCK] : -1;
-        leaf_work<R, D, FORM, COUNT, KEXT>(a, s, c1, c2, c3, c4, wc);
-        nq = 0;
-      }
-      // path steps run once a quarter of the working lanes stand at the end of
-      // their line, or when no lane steps (measured: 557, 574, 566 M path
-      // samples/s for 1/8, 1/4, 3/8; with the shared paths on the three-tori
-      // workload 1,279, 1,303, 1,280)
-      const bool at_end = st == ST_LINE && s.ni == kDone;
-      const int n_end = __popcll(__ballot(at_end));
-      const int stepping = __popcll(__ballot(st == ST_LINE && s.ni != kDone));
-      if (4 * n_end >= 64 - idle || stepping == 0) {
-        if (at_end) st = end_step<R, D, FORM, TRACE, COUNT, KEXT>(a, s, wc);
-      }
+      // the wavefront tests all the leaves that its lanes hold, then each lane
+      // handles the hits of its own line
+      const uint32_t hits = test_leaves<R, D, COUNT, BLOCK>(a, s, lbase, lo, wc);
+      if (hits != 0) leaf_hits<R, D, FORM, COUNT, KEXT, BLOCK>(a, s, hits, lbase, wc);
+      lo = lbase;
     }
   }
   if (COUNT) {
@@ -1170,10 +1291,19 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
   }
 }
 
+// The FP32 double layer is held to the 96 registers of five wavefronts per SIMD
+// (it takes 98 left to itself).
+template <typename R, int FORM, int EXT>
+constexpr int min_waves() { return sizeof(R) == 4 && FORM == F_DL && EXT == X_NONE ? 5 : 1; }
+
 template <typename R, int D, int FORM, bool TRACE, bool COUNT, int BLOCK, int EXT = X_NONE>
-__global__ void __launch_bounds__(BLOCK) walk_kernel(WalkArgs<R, D> a) {
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(min_waves<R, FORM, EXT>())))
+walk_kernel(WalkArgs<R, D> a) {
   __shared__ double red[(BLOCK / 64) * red_stride<EXT, D>()];
-  walk_block<R, D, FORM, TRACE, COUNT, BLOCK, EXT>(a, blockIdx.x, red);
+  // the argument where it lies in the kernel's argument segment (its only one)
+  const WalkArgs<R, D>& args = *(const WalkArgs<R, D>*)(const __attribute__((address_space(4))) WalkArgs<R, D>*)
+                                   __builtin_amdgcn_kernarg_segment_ptr();
+  walk_block<R, D, FORM, TRACE, COUNT, BLOCK, EXT>(args, blockIdx.x, red);
 }
 
 // Add-back of the control variate: out[p] (+)= an unbiased value of

@@ -3,9 +3,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <limits>
 #include <new>
 #include <vector>
 
@@ -18,10 +20,20 @@ using namespace wobi;
 
 namespace {
 
-// Leaves of at most two primitives: a leaf test loops over the most
-// primitives any parked lane has, so small leaves keep the lanes busy
-// (icosphere benchmark, leaves of at most 1 / 2 / 4: 72.5 / 68.9 / 71.2 ms).
-constexpr int kMaxLeaf = 2;
+// Leaves of at most two primitives (test_leaves tests a leaf's primitives side
+// by side, their records loaded together).
+constexpr int kMaxLeaf = wob::kLeafPrims;
+
+// FP32 triangle records lie 48 bytes apart up to this many triangles and 64
+// bytes apart, with the normal beside them, above.  Small scenes live in L2
+// and gain from the smaller footprint (20,480-triangle icosphere, 170,918
+// points x 256 paths: 51.1 ms against 53.0; its gradient walk 13.4 against
+// 13.7); scenes beyond L2 pay per line they touch (200,992-triangle tori,
+// 1M points x 512 paths: 326.0 ms against 313.7); at 61,000 both are equal.
+constexpr int64_t kPackedPrims = 40000;
+
+// Dynamic LDS that leaves 14 one-wavefront workgroups per CU (160 KB).
+constexpr size_t kLargeSceneLds = 45 * 256;
 
 // Round a double to binary16 toward -inf / +inf (|v| well inside the range).
 _Float16 step_h(_Float16 h, bool up) {
@@ -83,22 +95,91 @@ void store_box(const wobhost::Box& b, const double c[3], double k, Node& n, int 
   }
 }
 
-// An unused slot: an empty box (lo above hi on every axis), which no line
-// crosses, whatever the signs of its direction (both slab tests take the near
-// side by the direction's sign), and the entry kPop, so that even a crossed
-// empty slot would only pop the stack.
+// An unused slot: a box of NaN, which no line crosses (whatever the line, the
+// slab parameters are NaN on every axis and the comparison fails); its entry,
+// never taken, is a valid one (the first leaf).
 template <typename R, typename Node>
 void store_empty(Node& n, int which) {
   for (int a = 0; a < 3; ++a) {
-    if constexpr (sizeof(R) == 4) {
-      n.box[which][a] = 0x7bffu | (0xfbffu << 16);  // lo = +65504, hi = -65504 (binary16)
-    } else {
-      n.lo[which][a] = (R)1e300;
-      n.hi[which][a] = (R)-1e300;
+    if constexpr (sizeof(R) == 4) n.box[which][a] = 0x7e007e00u;  // binary16 NaN, twice
+    else n.lo[which][a] = n.hi[which][a] = (R)NAN;
+  }
+  n.child[which] = -1;
+}
+
+// Which entries a record holds: the choice that minimises the expected number
+// of records a line fetches (a line meets a box with probability proportional
+// to its measure).  cost(i, k) is that number below binary node i when i is
+// given k entries of its parent's record: one entry is a record of its own
+// (its measure, plus its children's cost with the record's kArity entries
+// dealt between them), more are dealt between its two children.  Against
+// opening the largest entry first: 3 % fewer fetches and, as the records are
+// fuller, 15-27 % fewer bytes (3.45 entries a record on the 200,992-triangle
+// tori, 3.09 before).
+// In the builder's flat array the second child of a node is the first node
+// after its first child's subtree.
+class Collapse {
+ public:
+  Collapse(const std::vector<wobhost::FlatNode>& nodes, int dim) : fn_(nodes), plan_(nodes.size()) {
+    std::vector<std::array<float, wob::kArity>> cost(nodes.size());  // [k - 1]
+    const double root = std::fmax(wobhost::box_measure(nodes[0].box, dim), 1e-300);
+    for (size_t i = nodes.size(); i-- > 0;) {
+      auto& c = cost[i];
+      auto& p = plan_[i];
+      p.fill(0);
+      if (nodes[i].child < 0) {
+        c.fill(0.f);
+        continue;
+      }
+      const auto& l = cost[first(i)];
+      const auto& r = cost[second(i)];
+      const auto deal = [&](int k, float best, uint8_t own) {
+        for (int q = 1; q < k; ++q)
+          if (l[q - 1] + r[k - q - 1] < best) {
+            best = l[q - 1] + r[k - q - 1];
+            own = (uint8_t)q;
+          }
+        return std::make_pair(best, own);
+      };
+      const auto record = deal(wob::kArity, std::numeric_limits<float>::infinity(), 1);
+      p[0] = record.second;
+      c[0] = (float)(wobhost::box_measure(nodes[i].box, dim) / root) + record.first;
+      for (int k = 2; k <= wob::kArity; ++k) {
+        const auto d = deal(k, c[k - 2], 0);  // 0: fewer entries do as well
+        c[k - 1] = d.first;
+        p[k - 1] = d.second;
+      }
     }
   }
-  n.child[which] = wob::kPop;
-}
+  // The entries (binary nodes) of the record of interior node i, at most
+  // max_ent (kArity, or 2: its children).
+  int entries(size_t i, int max_ent, size_t* out) const {
+    if (max_ent < wob::kArity) {
+      out[0] = first(i);
+      out[1] = second(i);
+      return 2;
+    }
+    const int n = open(first(i), plan_[i][0], out);
+    return n + open(second(i), wob::kArity - plan_[i][0], out + n);
+  }
+
+ private:
+  size_t first(size_t i) const { return (size_t)fn_[i].child; }
+  size_t second(size_t i) const { return (size_t)fn_[first(i)].skip; }
+  int open(size_t i, int k, size_t* out) const {
+    while (k > 1 && plan_[i][k - 1] == 0) --k;
+    if (k == 1 || fn_[i].child < 0) {
+      *out = i;
+      return 1;
+    }
+    const int q = plan_[i][k - 1], n = open(first(i), q, out);
+    return n + open(second(i), k - q, out + n);
+  }
+  const std::vector<wobhost::FlatNode>& fn_;
+  // [0]: entries of the node's own record given to its first child; [k - 1]:
+  // of k entries given to the node, those given to its first child
+  std::vector<std::array<uint8_t, wob::kArity>> plan_;
+};
 
 template <typename R, int D>
 wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int32_t* prims,
@@ -108,61 +189,48 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   using Prim = typename wob::Rec<R, D>::Prim;
   const int64_t T = sc->n_prims;
   // 4-wide interior records, in pre-order (a record's first interior child is
-  // the next record).  A record takes its binary node's two children and
-  // opens the interior entry of largest box measure until it holds kArity
-  // entries; every interior entry it keeps becomes a record of its own.  In
-  // the builder's flat array the first child of node i is node i + 1, the
-  // second the first node after the first child's subtree.
+  // the next record), each holding the entries that `collapse` chose below its
+  // binary node; every interior entry becomes a record of its own.
   const auto& fn = bvh.nodes;
-  const int dim = D;
   double fc[3], fk;
   box_frame<R>(fn[0].box, D, fc, fk);
   std::vector<Node> nodes;
+  nodes.reserve(fn.size() / 3 + 1);
   int max_ent = wob::kArity;
-  // deepest stack a line can need below a record: its own pushes (entries - 1)
-  // plus the deepest of its interior children
-  std::function<int32_t(size_t, int32_t*)> emit = [&](size_t i, int32_t* need) -> int32_t {
-    std::vector<size_t> ent = {(size_t)fn[i].child, (size_t)fn[(size_t)fn[i].child].skip};
-    while ((int)ent.size() < max_ent) {
-      int best = -1;
-      double bm = -1.0;
-      for (int q = 0; q < (int)ent.size(); ++q)
-        if (fn[ent[q]].child >= 0) {
-          const double mq = wobhost::box_measure(fn[ent[q]].box, dim);
-          if (mq > bm) {
-            bm = mq;
-            best = q;
-          }
-        }
-      if (best < 0) break;
-      const size_t c = ent[best];
-      ent.erase(ent.begin() + best);
-      ent.insert(ent.begin() + best, {(size_t)fn[c].child, (size_t)fn[(size_t)fn[c].child].skip});
-    }
+  const Collapse collapse(fn, D);
+  // need: the deepest stack that the subtree can take below what waits there
+  const std::function<int32_t(size_t, int32_t*)> emit = [&](size_t i, int32_t* need) -> int32_t {
+    size_t ent[wob::kArity];
+    const int n_ent = collapse.entries(i, max_ent, ent);
     const int32_t r = (int32_t)nodes.size();
     nodes.emplace_back();
-    std::memset(&nodes[r], 0, sizeof(Node));
-    int32_t deepest = 0;
-    int32_t child[wob::kArity];
-    for (int q = 0; q < (int)ent.size(); ++q) {
-      if (fn[ent[q]].child >= 0) {
-        int32_t sub = 0;
-        child[q] = emit(ent[q], &sub);
-        deepest = std::max(deepest, sub);
-      } else {
-        child[q] = fn[ent[q]].child;  // leaf code
-      }
+    int32_t child[wob::kArity], sub[wob::kArity];
+    for (int q = 0; q < n_ent; ++q) {
+      const auto& e = fn[ent[q]];
+      sub[q] = -1;
+      child[q] = e.child >= 0 ? emit(ent[q], &sub[q]) : e.child;  // a leaf's code
     }
-    Node& n = nodes[r];
+    // a line takes the crossed records of slot 0 first, then those of the
+    // last slot down to slot 1, and the k-th one from the last waits under k
+    // others: the record that needs the deepest stack is taken last (the
+    // 200,992-triangle tori need 17 entries, 28 with the records as they come)
+    int slot[wob::kArity];
+    for (int q = 0; q < n_ent; ++q) slot[q] = q;
+    std::stable_sort(slot, slot + n_ent, [&](int x, int y) { return sub[x] < sub[y]; });
+    *need = 0;
+    Node n;
+    std::memset(&n, 0, sizeof(Node));
     for (int q = 0; q < wob::kArity; ++q) {
-      if (q < (int)ent.size()) {
-        store_box<R, D>(fn[ent[q]].box, fc, fk, n, q);
-        n.child[q] = child[q];
+      const int at = (wob::kArity - q) % wob::kArity;  // the order in which slots are taken: 0, 3, 2, 1
+      if (q < n_ent) {
+        store_box<R, D>(fn[ent[slot[q]]].box, fc, fk, n, at);
+        n.child[at] = child[slot[q]];
+        if (sub[slot[q]] >= 0) *need = std::max(*need, n_ent - 1 - q + sub[slot[q]]);
       } else {
-        store_empty<R>(n, q);
+        store_empty<R>(n, at);
       }
     }
-    *need = (int32_t)ent.size() - 1 + deepest;
+    nodes[r] = n;
     return r;
   };
   int32_t need = 0;
@@ -170,7 +238,7 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   if (need > wob::kMaxDepth) {
     // a degenerate tree whose 4-wide records could push more than a lane's
     // stack holds: two entries per record (the binary tree, whose stack needs
-    // at most its depth - 1 entries)
+    // at most one entry per doubling of its leaves)
     nodes.clear();
     max_ent = 2;
     need = 0;
@@ -192,15 +260,19 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   sc->root = root;
   sc->stack_cap = std::max(need, 1);
   if (sc->stack_cap > wob::kMaxDepth) return WOB_E_MESH;
-  std::vector<Prim> recs((size_t)T);
-  std::vector<R> normals((size_t)T * 4, (R)0);
+  // the primitive records and, in their last bytes or in an array of their
+  // own, the unit normals
+  const bool wide = D == 3 && sizeof(R) == 4 && T > kPackedPrims;
+  const size_t stride = wide ? 64 : sizeof(Prim);
+  std::vector<unsigned char> recs((size_t)T * stride, 0);
+  std::vector<R> normals(wide ? 0 : (size_t)T * 4, (R)0);
   std::vector<int32_t> leaf_of_id((size_t)T);
   std::vector<double> area((size_t)T, 0.0);
   for (int64_t j = 0; j < T; ++j) {
     const int32_t id = bvh.order[j];
     leaf_of_id[id] = (int32_t)j;
-    Prim& p = recs[j];
-    std::memset(&p, 0, sizeof(Prim));
+    Prim& p = *reinterpret_cast<Prim*>(recs.data() + (size_t)j * stride);
+    R* const nrm = wide ? reinterpret_cast<R*>(recs.data() + (size_t)j * stride + sizeof(Prim)) : &normals[4 * (size_t)j];
     const int32_t* ix = prims + (int64_t)id * D;
     const int k = kind ? kind[id] : 0;
     p.idkind = id | (k << wob::kIdBits);
@@ -219,7 +291,7 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
       double n[3] = {e1d[1] * e2d[2] - e1d[2] * e2d[1], e1d[2] * e2d[0] - e1d[0] * e2d[2],
                      e1d[0] * e2d[1] - e1d[1] * e2d[0]};
       const double l = std::sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-      for (int a = 0; a < 3; ++a) normals[4 * j + a] = (R)(n[a] / l);
+      for (int a = 0; a < 3; ++a) nrm[a] = (R)(n[a] / l);
       area[id] = 0.5 * l;
     } else {
       for (int a = 0; a < 2; ++a) {
@@ -229,13 +301,14 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
         p.e[a] = (R)e1d[a];
       }
       const double l = std::sqrt(e1d[0] * e1d[0] + e1d[1] * e1d[1]);
-      normals[4 * j + 0] = (R)(e1d[1] / l);
-      normals[4 * j + 1] = (R)(-e1d[0] / l);
+      nrm[0] = (R)(e1d[1] / l);
+      nrm[1] = (R)(-e1d[0] / l);
       area[id] = l;
     }
   }
   sc->node_bytes = sizeof(Node);
-  sc->prim_bytes = sizeof(Prim);
+  sc->prim_bytes = (int64_t)stride;
+  sc->normal_offset = sizeof(Prim);
   // cumulative area fraction in caller-id order: summed in binary64, rounded
   // once to binary32 (an area-uniform pick compares a binary32 uniform with it)
   std::vector<float> cdf((size_t)T);
@@ -270,14 +343,14 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   // per-vertex boundary data
   std::vector<R> verts_r(v.size());
   for (size_t i = 0; i < v.size(); ++i) verts_r[i] = (R)v[i];
-  const size_t nb = std::max(nodes.size(), (size_t)1) * sizeof(Node), pb = recs.size() * sizeof(Prim),
+  const size_t nb = std::max(nodes.size(), (size_t)1) * sizeof(Node), pb = recs.size(),
                lb = leaf_of_id.size() * sizeof(int32_t), qb = normals.size() * sizeof(R),
                cb = sizeof(float) * T, vb = verts_r.size() * sizeof(R),
                ib = (size_t)T * D * sizeof(int32_t), sb = sizeof(unsigned long long),
                gb = guide.size() * sizeof(int32_t);
   if (hipMalloc(&sc->d_nodes, nb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc(&sc->d_prims, pb) != hipSuccess) return WOB_E_ALLOC;
-  if (hipMalloc(&sc->d_normals, qb) != hipSuccess) return WOB_E_ALLOC;
+  if (qb > 0 && hipMalloc(&sc->d_normals, qb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_leaf_of_id, lb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_area_cdf, cb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_area_guide, gb) != hipSuccess) return WOB_E_ALLOC;
@@ -288,7 +361,7 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   const auto put = [st](void* dst, const void* src, size_t bytes) {
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st) == hipSuccess;
   };
-  bool ok = put(sc->d_normals, normals.data(), qb) && put(sc->d_prims, recs.data(), pb) &&
+  bool ok = (qb == 0 || put(sc->d_normals, normals.data(), qb)) && put(sc->d_prims, recs.data(), pb) &&
             put(sc->d_leaf_of_id, leaf_of_id.data(), lb) && put(sc->d_area_cdf, cdf.data(), cb) &&
             put(sc->d_area_guide, guide.data(), gb) &&
             put(sc->d_verts, verts_r.data(), vb) && put(sc->d_vid, prims, ib) &&
@@ -315,7 +388,14 @@ void launch_form(const wob::WalkArgs<R, D>& a0, int mode, hipStream_t st) {
   a.lpp_shift = lpp_shift_for(a0.N, B, pooled);
   const int ppb = B >> a.lpp_shift;
   const dim3 grid((unsigned)((a.n_points + ppb - 1) / ppb)), block(B);
-  const size_t lds = wob::walk_lds_bytes(a.scene.stack_cap, B);  // traversal stacks, held leaves
+  size_t lds = wob::walk_lds_bytes(a.scene.stack_cap, B);  // traversal stacks, held leaves
+  // the double layer on a scene well beyond an XCD's 4 MB of L2: 14 wavefronts
+  // per CU instead of 17 fetch less over each other (200,000-triangle sphere,
+  // 100k points x 128 paths: 20.8 ms against 22.6; 98,000 triangles 17.9 against
+  // 18.0; the 20,480-triangle slice, within L2, 57.5 against 51.1, and the other
+  // forms, which run four wavefronts per SIMD or fewer, lose everywhere)
+  if (FORM == wob::F_DL && mode == MODE_SOLVE && !a0.grad_out && a0.scene.n_prims > kPackedPrims * 5 / 2)
+    lds = std::max(lds, (size_t)kLargeSceneLds);
   if constexpr (FORM != wob::F_FWD) {
     if (a.grad_out || a.path_grad_out) {  // value and gradient along the same paths
       if (mode == MODE_TRACE)
