@@ -56,6 +56,25 @@ constexpr int kMaxDepth = 60;
 // ones, where each then holds its unit normal in the last 16 bytes and never
 // straddles a 64-byte block (see prim_layout in the scene upload).
 template <typename R> struct alignas(sizeof(R) == 4 ? 16 : 32) Prim3 { R v0[3]; int32_t idkind; R e1[3]; R alpha; R e2[3]; int32_t pad; };
+// One primitive as a RIS candidate: all that its evaluation and, if it is
+// picked, the vertex on it need, in one 64-byte line (FP32), in caller-id order
+// (2D: third components zero).
+template <typename R> struct alignas(16 * sizeof(R)) Candidate {
+  R v0[3]; int32_t kind; R e1[3]; R alpha; R e2[3]; int32_t pad; R n[3];
+};
+// Entry b of the area CDF's guide (b = 0 .. 2^shift): the first index whose
+// cumulative area exceeds b / 2^shift, and that index's cumulative area.
+struct alignas(8) GuideEntry { int32_t first; float cdf; };
+struct GuideBucket { GuideEntry lo, hi; };
+// Entries b and b + 1, in one load.
+__device__ __forceinline__ GuideBucket guide_bucket(const GuideEntry* guide, uint32_t b) {
+  typedef int32_t entries_t __attribute__((ext_vector_type(4), aligned(8)));
+  entries_t v = *reinterpret_cast<const entries_t*>(guide + b);
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(v));  // else loaded word by word where each is used
+#endif
+  return __builtin_bit_cast(GuideBucket, v);
+}
 template <typename R> struct alignas(16) Prim2 { R v0[2]; R e[2]; R alpha; int32_t idkind; };
 
 template <typename R, int D> struct Rec;
@@ -75,9 +94,8 @@ struct SceneView {
   uint32_t prim_stride, normal_stride;
   const int32_t* leaf_of_id;  // caller id -> leaf-order index
   const float* area_cdf;      // caller-id order, cumulative area / |Gamma| (binary32, last 1)
-  // guide[b] = the first index whose area_cdf exceeds b / 2^guide_shift
-  // (b = 0 .. 2^guide_shift; the last entry n_prims - 1)
-  const int32_t* area_guide;
+  const GuideEntry* area_guide;  // 2^guide_shift + 1 entries (the last: n_prims - 1)
+  const Candidate<R>* candidates;  // caller-id order
   int32_t guide_shift;
   R area_total;               // |Gamma|
   int32_t n_nodes;            // interior records
@@ -220,6 +238,21 @@ __device__ __forceinline__ PrimGeo<R> load_prim(const char* prims, uint32_t stri
 template <typename R, int D>
 __device__ __forceinline__ PrimGeo<R> load_prim(const SceneView<R, D>& s, int32_t idx) {
   return load_prim<R, D>(s.prims, s.prim_stride, idx);
+}
+
+template <typename R, int D>
+__device__ __forceinline__ PrimGeo<R> candidate_geo(const Candidate<R>& c, int32_t id) {
+  PrimGeo<R> g;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    g.v0[a] = a < D ? c.v0[a] : (R)0;
+    g.e1[a] = a < D ? c.e1[a] : (R)0;
+    g.e2[a] = D == 3 ? c.e2[a] : (R)0;
+  }
+  g.alpha = c.alpha;
+  g.id = id;
+  g.kind = c.kind;
+  return g;
 }
 
 // Unit normal pointing out of Omega.  Computed on the host in binary64 from

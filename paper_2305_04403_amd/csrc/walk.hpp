@@ -164,7 +164,7 @@ struct PathState {
   R x0[3];
   int32_t prim0;
   R x[3], W, acc;
-  int32_t cur_idx, i;
+  int32_t cur_idx, i;    // the vertex's primitive in leaf order (RIS: caller id), -1 off the boundary
   int32_t* vp;           // per-line records (trace mode)
   int32_t* vm;
   uint32_t z;            // counter word 2 of the current line
@@ -220,6 +220,13 @@ __device__ __forceinline__ void fwd_end(const WalkArgs<R, D>& a, const PathState
 // candidate j when u_j S_j < |k_j|; weight sign(k) S |Gamma| / C.  Moves the
 // path to the kept point and adds its emission; returns false when no
 // candidate carries kernel mass (the path ends).
+// A candidate costs two lines of memory, its guide bucket and its record (with
+// the guide's and the CDF's own arrays, the leaf index and the leaf-ordered
+// record it was four or five, and random lines from L2 are what bounds the
+// walk: 100k tori points x 64 paths, 16 candidates, 7.0 -> 4.5 ms; 30,600
+// triangles, 113k points x 67 paths, 32 candidates, 15.7 -> 8.9 ms).  Fetching
+// two or four candidates together was slower (5.2, 5.3 ms against 4.9): their
+// registers cost more wavefronts than the loads gained.
 // CV (corrected walk, 3D single layer): given the candidates, the pick's
 // expected contribution w F(y_pick) is (|Gamma| / C) sum_j k(y_j) F(y_j); the
 // step adds that sum and subtracts w F(y_pick), with F as for line sampling
@@ -237,17 +244,24 @@ __device__ __forceinline__ bool ris_step(const WalkArgs<R, D>& a, PathState<R, D
   R csum = 0;
   for (int j = 0; j < a.ris_c; ++j) {
     const U4 rj = philox(s.path, s.point, s.z | 3u, (uint32_t)j, a.k0, a.k1);
+    // the first caller id whose cdf exceeds u: the first one of its guide
+    // bucket, or searched among the bucket's others
     const float u = unit<float>(rj.x);
-    // the first caller id whose cdf exceeds u, searched in its guide bucket
     const uint32_t bkt = (uint32_t)(u * (float)(1u << sc.guide_shift));
-    int32_t lo = sc.area_guide[bkt], hi = sc.area_guide[bkt + 1];
-    while (lo < hi) {
-      const int32_t mid = (lo + hi) >> 1;
-      if (sc.area_cdf[mid] > u) hi = mid;
-      else lo = mid + 1;
+    const GuideBucket bk = guide_bucket(sc.area_guide, bkt);
+    const GuideEntry lo = bk.lo, hi = bk.hi;
+    int32_t id = lo.first;
+    if (id < hi.first && !(lo.cdf > u)) {
+      int32_t l = id + 1, h = hi.first;
+      while (l < h) {
+        const int32_t mid = (l + h) >> 1;
+        if (sc.area_cdf[mid] > u) h = mid;
+        else l = mid + 1;
+      }
+      id = l;
     }
-    const int32_t leaf = sc.leaf_of_id[lo];
-    const PrimGeo<R> g = load_prim<R, D>(sc, leaf);
+    const Candidate<R> cand = sc.candidates[id];
+    const PrimGeo<R> g = candidate_geo<R, D>(cand, id);
     R bu = unit<R>(rj.y), bv = D == 3 ? unit<R>(rj.z) : (R)0;
     if (bu + bv > (R)1) {
       bu = (R)1 - bu;
@@ -281,7 +295,7 @@ __device__ __forceinline__ bool ris_step(const WalkArgs<R, D>& a, PathState<R, D
     const R pk = fabs(k);
     S += pk;
     if (unit<R>(rj.w) * S < pk) {
-      lpick = leaf;
+      lpick = g.id;
       kpick = k;
       ypick[0] = y[0];
       ypick[1] = y[1];
@@ -289,9 +303,7 @@ __device__ __forceinline__ bool ris_step(const WalkArgs<R, D>& a, PathState<R, D
     }
     if constexpr (CV) {
       if (sum) {  // the candidate's term of the all-candidates sum
-        R cn[3];
-        load_normal<R, D>(sc, leaf, cn);
-        const R e = sl_emission<R, D, VD>(a, g, cn, y, s.i + 1 >= a.M);
+        const R e = sl_emission<R, D, VD>(a, g, cand.n, y, s.i + 1 >= a.M);
         csum += k * (last ? e : e + a.cv_g[g.id]);
       }
     }
@@ -322,9 +334,9 @@ __device__ __forceinline__ bool ris_step(const WalkArgs<R, D>& a, PathState<R, D
   s.x[1] = ypick[1];
   s.x[2] = ypick[2];
   s.cur_idx = lpick;
-  const PrimGeo<R> gn = load_prim<R, D>(sc, lpick);
-  R nn[3];
-  load_normal<R, D>(sc, lpick, nn);
+  const Candidate<R> picked = sc.candidates[lpick];
+  const PrimGeo<R> gn = candidate_geo<R, D>(picked, lpick);
+  const R nn[3] = {picked.n[0], picked.n[1], picked.n[2]};
   if (TRACE && s.vp) s.vp[s.i] = gn.id;
   if constexpr (CV) {
     if (s.i == 0) {  // the line-0 table subtracted, the emission kept
@@ -351,8 +363,16 @@ __device__ __forceinline__ int begin_step(const WalkArgs<R, D>& a, PathState<R, 
   s.on_gamma = s.cur_idx >= 0;
   s.z = (a.problem << 24) | ((uint32_t)s.i << 8);
   if (s.on_gamma && FORM != F_DL && FORM != F_FWD) {
-    s.gc = load_prim<R, D>(a.scene, s.cur_idx);
-    load_normal<R, D>(a.scene, s.cur_idx, s.nc);
+    if constexpr (FORM == F_SL_RIS) {
+      const Candidate<R> on = a.scene.candidates[s.cur_idx];
+      s.gc = candidate_geo<R, D>(on, s.cur_idx);
+      s.nc[0] = on.n[0];
+      s.nc[1] = on.n[1];
+      s.nc[2] = on.n[2];
+    } else {
+      s.gc = load_prim<R, D>(a.scene, s.cur_idx);
+      load_normal<R, D>(a.scene, s.cur_idx, s.nc);
+    }
   }
   // step 0 from an evaluation point uses the representation formula; in
   // density mode x0 is itself a vertex of the boundary recursion
@@ -554,7 +574,8 @@ __device__ __forceinline__ int start_path(const WalkArgs<R, D>& a0, PathState<R,
       asm volatile("");  // else merged with other stores, and the state moved to scratch
       return ST_DONE;
     }
-    s.cur_idx = s.prim0 >= 0 ? a.scene.leaf_of_id[s.prim0] : -1;
+    if constexpr (FORM == F_SL_RIS) s.cur_idx = s.prim0;
+    else s.cur_idx = s.prim0 >= 0 ? a.scene.leaf_of_id[s.prim0] : -1;
     s.x[0] = s.x0[0];
     s.x[1] = s.x0[1];
     s.x[2] = s.x0[2];
@@ -1477,6 +1498,25 @@ __global__ void sample_boundary_kernel(SceneView<R, D> s, const float* __restric
   hit_point(g, a, b, y);
   for (int k = 0; k < D; ++k) points[i * D + k] = y[k];
   prim_out[i] = g.id;
+}
+
+// The RIS candidates' records, from the primitive records and normals.
+template <typename R, int D>
+__global__ void __launch_bounds__(256) candidate_kernel(SceneView<R, D> s, Candidate<R>* out) {
+  const int32_t j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= s.n_prims) return;
+  const PrimGeo<R> g = load_prim<R, D>(s, j);
+  Candidate<R> c;
+  load_normal<R, D>(s, j, c.n);
+  for (int k = 0; k < 3; ++k) {
+    c.v0[k] = g.v0[k];
+    c.e1[k] = g.e1[k];
+    c.e2[k] = g.e2[k];
+  }
+  c.alpha = g.alpha;
+  c.kind = g.kind;
+  c.pad = 0;
+  out[g.id] = c;
 }
 
 // Centroid of every primitive, written at its caller id (3D).

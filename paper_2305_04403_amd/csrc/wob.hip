@@ -329,13 +329,13 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   int shift = 0;
   while ((int64_t)1 << shift < T && shift < 24) ++shift;
   const int64_t K = (int64_t)1 << shift;
-  std::vector<int32_t> guide((size_t)K + 1);
+  std::vector<wob::GuideEntry> guide((size_t)K + 1);
   {
     int64_t i = 0;
     for (int64_t b = 0; b <= K; ++b) {
       const double t = (double)b / (double)K;
       while (i < T - 1 && !((double)cdf[i] > t)) ++i;
-      guide[b] = (int32_t)i;
+      guide[b] = wob::GuideEntry{(int32_t)i, cdf[i]};
     }
   }
   sc->guide_shift = shift;
@@ -347,13 +347,14 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
                lb = leaf_of_id.size() * sizeof(int32_t), qb = normals.size() * sizeof(R),
                cb = sizeof(float) * T, vb = verts_r.size() * sizeof(R),
                ib = (size_t)T * D * sizeof(int32_t), sb = sizeof(unsigned long long),
-               gb = guide.size() * sizeof(int32_t);
+               gb = guide.size() * sizeof(wob::GuideEntry), db = (size_t)T * sizeof(wob::Candidate<R>);
   if (hipMalloc(&sc->d_nodes, nb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc(&sc->d_prims, pb) != hipSuccess) return WOB_E_ALLOC;
   if (qb > 0 && hipMalloc(&sc->d_normals, qb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_leaf_of_id, lb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_area_cdf, cb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_area_guide, gb) != hipSuccess) return WOB_E_ALLOC;
+  if (hipMalloc(&sc->d_candidates, db) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc(&sc->d_verts, vb) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_vid, ib) != hipSuccess) return WOB_E_ALLOC;
   if (hipMalloc((void**)&sc->d_status, sb) != hipSuccess) return WOB_E_ALLOC;
@@ -367,10 +368,15 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
             put(sc->d_verts, verts_r.data(), vb) && put(sc->d_vid, prims, ib) &&
             hipMemsetAsync(sc->d_status, 0, sb, st) == hipSuccess;
   if (ok && !nodes.empty()) ok = put(sc->d_nodes, nodes.data(), nodes.size() * sizeof(Node));
+  if (ok) {
+    hipLaunchKernelGGL((wob::candidate_kernel<R, D>), dim3((unsigned)((T + 255) / 256)), dim3(256), 0, st,
+                       view<R, D>(sc), (wob::Candidate<R>*)sc->d_candidates);
+    ok = hipGetLastError() == hipSuccess;
+  }
   // the copies must end before the host arrays are released, also on failure
   if (hipStreamSynchronize(st) != hipSuccess || !ok) return WOB_E_DEVICE;
   sc->n_verts = (int64_t)(v.size() / D);
-  sc->device_bytes = (int64_t)(nb + pb + lb + qb + cb + vb + ib + sb + gb);
+  sc->device_bytes = (int64_t)(nb + pb + lb + qb + cb + vb + ib + sb + gb + db);
   return WOB_OK;
 }
 
@@ -676,6 +682,7 @@ void wob_free(wob_scene sc) {
   if (sc->d_normals) (void)hipFree(sc->d_normals);
   if (sc->d_area_cdf) (void)hipFree(sc->d_area_cdf);
   if (sc->d_area_guide) (void)hipFree(sc->d_area_guide);
+  if (sc->d_candidates) (void)hipFree(sc->d_candidates);
   if (sc->d_leaf_of_id) (void)hipFree(sc->d_leaf_of_id);
   if (sc->d_status) (void)hipFree(sc->d_status);
   if (sc->d_verts) (void)hipFree(sc->d_verts);
