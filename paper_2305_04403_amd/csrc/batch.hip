@@ -65,7 +65,7 @@ inline bool any_vertex_data(const wob_problem* p, int32_t n) {
 // the walk arguments of problem order[i] at args[i], tile offsets off[0..n],
 // and the deepest traversal stack of the problems' scenes.
 template <typename R, int D>
-wob_status fill_table(const wob_problem* probs, const int32_t* order, int n, int block,
+wob_status fill_table(const wob_problem* probs, const int32_t* order, int n, int block, int32_t n_cu,
                       wob::WalkArgs<R, D>* args, int64_t* off, int32_t* stack_cap) {
   off[0] = 0;
   *stack_cap = 1;
@@ -81,12 +81,15 @@ wob_status fill_table(const wob_problem* probs, const int32_t* order, int n, int
     // the kernel runs the X_VDATA instantiation for every problem when one
     // gives its data per vertex; the plain single-layer forms pool two points
     // per lane group in the other (the same rule as the kernel's)
-    a.lpp_shift = lpp_shift_for(p.samples, block,
-                                wob::pools_points(a.form, vdata ? wob::X_VDATA : wob::X_NONE, false, false));
+    const LaneSplit split =
+        split_lanes<R>(wob::pools_points(a.form, vdata ? wob::X_VDATA : wob::X_NONE, false, false),
+                       p.scene->stack_cap, p.n_points, p.samples, n_cu);
+    a.lpp_shift = split.shift;
+    if (split.spread) a.form |= wob::kFormSpread;
     a.mean_out = (R*)p.mean_out;
     a.var_out = (R*)p.var_out;
     args[i] = a;
-    const int64_t ppt = block >> a.lpp_shift;
+    const int64_t ppt = std::max(1, block >> a.lpp_shift);
     off[i + 1] = off[i] + (p.n_points + ppt - 1) / ppt;
   }
   return WOB_OK;
@@ -97,7 +100,7 @@ wob_status upload_table(wob_batch_s* b, int block) {
   const int n = (int)b->probs.size();
   std::vector<wob::WalkArgs<R, D>> args(n);
   std::vector<int64_t> off(n + 1, 0);
-  const wob_status fs = fill_table<R, D>(b->probs.data(), b->order.data(), n, block, args.data(), off.data(),
+  const wob_status fs = fill_table<R, D>(b->probs.data(), b->order.data(), n, block, b->n_cu, args.data(), off.data(),
                                          &b->stack_cap);
   if (fs != WOB_OK) return fs;
   if (!b->d_args && hipMalloc(&b->d_args, sizeof(wob::WalkArgs<R, D>) * n) != hipSuccess)
@@ -270,13 +273,13 @@ wob_status solve_static(const wob_problem* problems, int32_t n, const int32_t* o
   int64_t off[WOB_STATIC_MAX_PROBLEMS + 1];
   int32_t stack_cap = 1;
   wob_tune tune = given ? *given : wob_tune{256, 4};
-  wob_status s = fill_table<R, D>(problems, order, n, tune.block, args, off, &stack_cap);
+  wob_status s = fill_table<R, D>(problems, order, n, tune.block, n_cu, args, off, &stack_cap);
   if (s != WOB_OK) return s;
   if (!fits_lds_cap(stack_cap, max_lds, tune.block)) {
     // as wob_batch_create: the default shape falls back to the smallest workgroup
     if (given) return WOB_E_ARG;
     tune = wob_tune{128, 8};
-    s = fill_table<R, D>(problems, order, n, tune.block, args, off, &stack_cap);
+    s = fill_table<R, D>(problems, order, n, tune.block, n_cu, args, off, &stack_cap);
     if (s != WOB_OK) return s;
     if (!fits_lds_cap(stack_cap, max_lds, tune.block)) return WOB_E_ARG;
   }

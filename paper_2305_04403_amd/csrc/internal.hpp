@@ -11,6 +11,7 @@
 
 struct wob_scene_s {
   int32_t dim = 0, precision = 0, device = 0;
+  int32_t n_cu = 0;       // compute units of the device
   int64_t n_prims = 0, n_nodes = 0, n_leaves = 0, n_verts = 0;
   int32_t n_inner = 0;    // interior records on the device
   int32_t root = 0;       // root entry (record 0, or a leaf)
@@ -44,10 +45,12 @@ namespace wobi {
 constexpr int kSolveBlock = 64;
 
 // Paths per lane, on average (the lanes of a point share its paths and take
-// the next one as theirs end): fixes the lanes per point.  Measured with 4, 8
-// and 16: three-tori workload (512 paths) 1,301 / 1,300 / 1,110 M path
-// samples/s, icosphere slice (256 paths) 747 / 767 / 769 M.
-constexpr int kPathsPerLane = 8;
+// the next one as theirs end): fixes the lanes per point.  Measured with 8, 4
+// and 2: gradient walk of 60k points x 128 paths 12.02 / 12.05 / 11.19 ms, batch
+// of 16 problems 36.8 / 36.4 / 36.0, RIS 4.36 / 4.37 / 4.28, single layer on
+// 100k points x 64 paths 4.78 / 4.28 / 4.39; the three-tori workload (512
+// paths: 32 lanes either way) 313.2 / 313.6 / 313.3.
+constexpr int kPathsPerLane = 2;
 
 // log2 of the lanes that share one point: the smallest power of two >=
 // ceil(N / kPathsPerLane), at most the block (a wavefront holds several points
@@ -59,6 +62,48 @@ inline int lpp_shift_for(int32_t samples, int block, bool pooled = false) {
   int s = 0;
   while ((1 << s) < lanes && (1 << s) < cap) ++s;
   return s;
+}
+
+// The same for a solve of few paths: the lanes per point are doubled, down to
+// one path per lane, while the launch is short of wavefronts.  Up to 64 lanes
+// per point the line lies at 64 wavefronts per CU, four times what is resident
+// (with 16 / 32 / 64 per CU: single layer on 30k points x 128 paths 3.24 / 2.87 /
+// 2.74 ms, double layer on 20k x 64 1.72 / 1.46 / 1.37): shorter wavefronts wait
+// less for their slowest lane.  Beyond, a point takes several wavefronts of one
+// workgroup, which wait for each other: up to 8 per CU (exterior Neumann, 4,000
+// points x 128 paths: 0.37 ms with 64 lanes per point, 0.48 with 128; 16
+// points x 256 paths: 1.65 ms with 32 lanes, 0.25 with 256).
+inline int spread_shift(int shift, int max_shift, int64_t n_points, int32_t samples, int32_t n_cu) {
+  while (shift < max_shift && ((int64_t)1 << shift) < samples &&
+         (n_points << shift) < (int64_t)n_cu * 64 * (shift < 6 ? 64 : 8))
+    ++shift;
+  // a launch takes less than 2^32 lanes
+  while (shift > 0 && (n_points << shift) >> 31) --shift;
+  return shift;
+}
+
+// The lanes of a point of a plain solve, in a launch of its own and in a batch
+// alike (so the two merge their statistics in the same order): `spread` where
+// the walk leaves the pools of two points or takes more than a wavefront per
+// point, in workgroups of up to 256 or kWideBlock lanes, as the LDS of the scene's
+// stacks allows.
+template <typename R>
+constexpr int kWideBlock = sizeof(R) == 4 ? 1024 : 512;
+
+struct LaneSplit {
+  int shift;
+  bool spread;
+};
+
+template <typename R>
+LaneSplit split_lanes(bool pooled, int32_t stack_cap, int64_t n_points, int32_t samples, int32_t n_cu) {
+  constexpr size_t lds_limit = 160 * 1024 - 1024;
+  const int most = wob::walk_lds_bytes(stack_cap, kWideBlock<R>) <= lds_limit ? (kWideBlock<R> == 1024 ? 10 : 9)
+                   : wob::walk_lds_bytes(stack_cap, 256) <= lds_limit         ? 8
+                                                                              : 6;
+  const int shift0 = lpp_shift_for(samples, kSolveBlock, pooled);
+  const int shift = spread_shift(shift0, most, n_points, samples, n_cu);
+  return {shift, shift > shift0 && (pooled || shift > 6)};
 }
 
 template <typename R, int D>

@@ -44,7 +44,7 @@ struct WalkArgs {
   uint32_t problem;           // problem index (counter word 2, bits 24..31)
   int32_t lpp_shift;          // log2 of lanes per point (0 .. log2 of the block size)
   int32_t path_offset;        // path k of a point draws the random numbers of path path_offset + k
-  int32_t form;               // F_DL / F_DIRECT / F_SL / F_SL_RIS (read by the batched kernel)
+  int32_t form;               // F_DL / F_DIRECT / F_SL / F_SL_RIS, | kFormSpread (read by the batched kernel)
   int32_t density;            // estimate the boundary unknown at boundary points (no own emission)
   int32_t ris_c;              // single layer: RIS candidates per vertex, 0 = line sampling
   uint32_t mixed_thr;         // single layer, Dirichlet vertices: floor(p_k 2^24)
@@ -134,8 +134,11 @@ enum { ST_NONE = 0, ST_LINE = 1, ST_DONE = 2, ST_STEP = 3 };
 // X_VDATA is a flag on top of either: the boundary data may be given per
 // vertex (a separate instantiation, so the program-data kernels do not carry
 // the interpolation's registers).
-enum Ext { X_NONE = 0, X_CV = 1, X_GRAD = 2, X_VDATA = 4 };
+// X_SPREAD: a solve of few paths, its points' lanes not pooled (see
+// spread_shift).
+enum Ext { X_NONE = 0, X_CV = 1, X_GRAD = 2, X_VDATA = 4, X_SPREAD = 8 };
 constexpr int ext_kind(int ext) { return ext & 3; }
+constexpr int kFormSpread = 16;  // in WalkArgs::form: X_SPREAD for this problem of a batch
 constexpr bool ext_vdata(int ext) { return (ext & X_VDATA) != 0; }
 
 // Solves whose lane groups pool the paths of two points (the plain
@@ -818,7 +821,9 @@ __device__ __forceinline__ int end_step(const WalkArgs<R, D>& a0, PathState<R, D
       // G / p (times -k / p_k at a Dirichlet vertex)
       w = s.gscale * (D == 3 ? mm * rho / ((R)2 * acy) : -mm * rho * log(rho) / ((R)2 * acy));
     } else {
-      const R cx = sgn_t * dot3(s.d, s.nc);
+      // the contraction written out: the kernels of one path's value on
+      // different lane splits must round it alike
+      const R cx = sgn_t * fma(s.d[2], s.nc[2], fma(s.d[0], s.nc[0], s.d[1] * s.nc[1]));
       w = D == 3 ? -phi * mm * (cx + s.gc.alpha * rho) / acy
                  : -phi * mm * (cx - s.gc.alpha * rho * log(rho)) / acy;
     }
@@ -928,12 +933,15 @@ __device__ __forceinline__ void chan_merge(double& n, double& mean, double& m2, 
 // 2 lpp lanes of points 2j, 2j + 1 take c = 0 .. 2N - 1 as (point c >= N,
 // path c mod N), which halves the time the lanes wait for the group's last
 // paths.  A path's value depends on its index only, not on the lane.
-// `red` is BLOCK / 64 x red_stride<EXT, D>() doubles of LDS.
+// `red` is BLOCK / 64 x red_stride<EXT, D>() doubles of LDS.  PARTS (the batched
+// kernel): a point of more than BLOCK lanes is walked BLOCK lanes at a time, one
+// call for each `part` in turn, its statistics so far in three more doubles of
+// `red`; its wavefronts share no paths, so they need not run at once.
 template <int EXT, int D>
 constexpr int red_stride() { return ext_kind(EXT) == X_GRAD ? 3 + 2 * D : 3; }
 
-template <typename R, int D, int FORM, bool TRACE, bool COUNT, int BLOCK, int EXT = X_NONE>
-__device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t block_index, double* red) {
+template <typename R, int D, int FORM, bool TRACE, bool COUNT, int BLOCK, int EXT = X_NONE, bool PARTS = false>
+__device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t block_index, double* red, int part = 0) {
   const int tid = threadIdx.x;
   const int lpp = 1 << a.lpp_shift;
   constexpr bool POOL = pools_points(FORM, EXT, TRACE, COUNT);
@@ -942,8 +950,8 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
   const int gshift = POOL ? a.lpp_shift + 1 : (a.lpp_shift < 6 ? a.lpp_shift : 6);
   const int G = 1 << gshift;
   const int64_t point0 =
-      block_index * (BLOCK >> a.lpp_shift) + (POOL ? ((tid >> a.lpp_shift) & ~1) : (tid >> a.lpp_shift));
-  const int lane_in_point = tid & (lpp - 1);
+      block_index * (PARTS && lpp > BLOCK ? 1 : BLOCK >> a.lpp_shift) + (POOL ? ((tid >> a.lpp_shift) & ~1) : (tid >> a.lpp_shift));
+  const int lane_in_point = (PARTS ? tid + part * BLOCK : tid) & (lpp - 1);
   // the group's next free counter, in LDS after the held leaves
   // (the first G counters start at once); only this wavefront reads and
   // writes it
@@ -1291,6 +1299,23 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
     }
   }
   __syncthreads();
+  if (PARTS && lpp > BLOCK) {
+    if (tid == 0) {  // the wavefronts in order, as one workgroup of the point merges them
+      double* const sum = red + (BLOCK / 64) * RS;
+      double tn = part ? sum[0] : red[0], tm = part ? sum[1] : red[1], ts = part ? sum[2] : red[2];
+      for (int w = part ? 0 : 1; w < BLOCK / 64; ++w)
+        chan_merge(tn, tm, ts, red[w * RS + 0], red[w * RS + 1], red[w * RS + 2]);
+      sum[0] = tn;
+      sum[1] = tm;
+      sum[2] = ts;
+      if ((part + 1) * BLOCK == lpp) {
+        a.mean_out[point0] = tn > 0.0 ? (R)tm : (R)NAN;
+        if (a.var_out) a.var_out[point0] = (R)(tn > 1.0 ? ts / (tn - 1.0) : 0.0);
+      }
+    }
+    __syncthreads();  // the next part writes `red` again
+    return;
+  }
   if (lane_in_point == 0 && point0 < a.n_points) {
     const int waves = lpp >> 6;
     double tn = red[wave * RS + 0], tm = red[wave * RS + 1], ts = red[wave * RS + 2];
@@ -1539,7 +1564,7 @@ __global__ void __launch_bounds__(BLOCK) batch_kernel(const WalkArgs<R, D>* __re
                                                       const int64_t* __restrict__ tile_off,
                                                       int32_t n_probs, int64_t stride,
                                                       unsigned long long* __restrict__ counter) {
-  __shared__ double red[(BLOCK / 64) * 3];
+  __shared__ double red[(BLOCK / 64 + 1) * 3];
   __shared__ long long s_tile;
   const int64_t n_tiles = tile_off[n_probs];
   for (;;) {
@@ -1558,10 +1583,20 @@ __global__ void __launch_bounds__(BLOCK) batch_kernel(const WalkArgs<R, D>* __re
     const WalkArgs<R, D>& a = probs[b];
     const int64_t local = tile - tile_off[b];
     const int form = __builtin_amdgcn_readfirstlane(a.form);
-    if (form == F_DL) walk_block<R, D, F_DL, false, false, BLOCK, VX>(a, local, red);
-    else if (form == F_DIRECT) walk_block<R, D, F_DIRECT, false, false, BLOCK, VX>(a, local, red);
-    else if (form == F_SL_RIS) walk_block<R, D, F_SL_RIS, false, false, BLOCK, VX>(a, local, red);
-    else walk_block<R, D, F_SL, false, false, BLOCK, VX>(a, local, red);
+    const int parts = (1 << a.lpp_shift) > BLOCK ? (1 << a.lpp_shift) / BLOCK : 1;
+    for (int part = 0; part < parts; ++part) {
+      if (form == (F_DIRECT | kFormSpread))
+        walk_block<R, D, F_DIRECT, false, false, BLOCK, VX | X_SPREAD, true>(a, local, red, part);
+      else if (form == (F_SL_RIS | kFormSpread))
+        walk_block<R, D, F_SL_RIS, false, false, BLOCK, VX | X_SPREAD, true>(a, local, red, part);
+      else if (form == (F_SL | kFormSpread))
+        walk_block<R, D, F_SL, false, false, BLOCK, VX | X_SPREAD, true>(a, local, red, part);
+      else if ((form & ~kFormSpread) == F_DL)
+        walk_block<R, D, F_DL, false, false, BLOCK, VX, true>(a, local, red, part);
+      else if (form == F_DIRECT) walk_block<R, D, F_DIRECT, false, false, BLOCK, VX>(a, local, red);
+      else if (form == F_SL_RIS) walk_block<R, D, F_SL_RIS, false, false, BLOCK, VX>(a, local, red);
+      else walk_block<R, D, F_SL, false, false, BLOCK, VX>(a, local, red);
+    }
   }
 }
 

@@ -382,16 +382,36 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
 
 enum Mode { MODE_SOLVE = 0, MODE_TRACE = 1, MODE_COUNT = 2 };
 
+// A plain solve with 2^lpp_shift lanes per point in workgroups of B lanes.
+template <typename R, int D, int FORM, int VX, int B>
+void launch_spread(const wob::WalkArgs<R, D>& a, hipStream_t st) {
+  const int ppb = B >> a.lpp_shift;
+  hipLaunchKernelGGL((wob::walk_kernel<R, D, FORM, false, false, B, wob::X_SPREAD | VX>),
+                     dim3((unsigned)((a.n_points + ppb - 1) / ppb)), dim3(B),
+                     wob::walk_lds_bytes(a.scene.stack_cap, B), st, a);
+}
+
 // VX: X_VDATA for per-vertex data (its own instantiation of each kernel)
 template <typename R, int D, int FORM, int VX>
-void launch_form(const wob::WalkArgs<R, D>& a0, int mode, hipStream_t st) {
+void launch_form(const wob::WalkArgs<R, D>& a0, int mode, int32_t n_cu, hipStream_t st) {
   constexpr int B = kSolveBlock;
   // plain single-layer solves pool two points per lane group: at most 32
   // lanes per point (the kernel instantiation decides, by the same rule)
-  const bool pooled = mode == MODE_SOLVE && !(a0.grad_out || a0.path_grad_out) && !a0.cv_g &&
-                      wob::pools_points(FORM, VX, false, false);
+  const bool plain = mode == MODE_SOLVE && !(a0.grad_out || a0.path_grad_out) && !a0.cv_g;
+  const bool pooled = plain && wob::pools_points(FORM, VX, false, false);
   wob::WalkArgs<R, D> a = a0;
-  a.lpp_shift = lpp_shift_for(a0.N, B, pooled);
+  if (plain) {
+    const LaneSplit split = split_lanes<R>(pooled, a.scene.stack_cap, a.n_points, a.N, n_cu);
+    a.lpp_shift = split.shift;
+    if (split.spread) {
+      if (split.shift <= 6) launch_spread<R, D, FORM, VX, 64>(a, st);
+      else if (split.shift <= 8) launch_spread<R, D, FORM, VX, 256>(a, st);
+      else launch_spread<R, D, FORM, VX, kWideBlock<R>>(a, st);
+      return;
+    }
+  } else {
+    a.lpp_shift = spread_shift(lpp_shift_for(a.N, B), 6, a.n_points, a.N, n_cu);
+  }
   const int ppb = B >> a.lpp_shift;
   const dim3 grid((unsigned)((a.n_points + ppb - 1) / ppb)), block(B);
   size_t lds = wob::walk_lds_bytes(a.scene.stack_cap, B);  // traversal stacks, held leaves
@@ -434,17 +454,17 @@ void launch_form(const wob::WalkArgs<R, D>& a0, int mode, hipStream_t st) {
 }
 
 template <typename R, int D, int VX>
-void launch_walk_vx(const wob::WalkArgs<R, D>& a, int mode, hipStream_t st) {
-  if (a.form == wob::F_DL) launch_form<R, D, wob::F_DL, VX>(a, mode, st);
-  else if (a.form == wob::F_DIRECT) launch_form<R, D, wob::F_DIRECT, VX>(a, mode, st);
-  else if (a.form == wob::F_SL_RIS) launch_form<R, D, wob::F_SL_RIS, VX>(a, mode, st);
-  else launch_form<R, D, wob::F_SL, VX>(a, mode, st);
+void launch_walk_vx(const wob::WalkArgs<R, D>& a, int mode, int32_t n_cu, hipStream_t st) {
+  if (a.form == wob::F_DL) launch_form<R, D, wob::F_DL, VX>(a, mode, n_cu, st);
+  else if (a.form == wob::F_DIRECT) launch_form<R, D, wob::F_DIRECT, VX>(a, mode, n_cu, st);
+  else if (a.form == wob::F_SL_RIS) launch_form<R, D, wob::F_SL_RIS, VX>(a, mode, n_cu, st);
+  else launch_form<R, D, wob::F_SL, VX>(a, mode, n_cu, st);
 }
 
 template <typename R, int D>
-void launch_walk(const wob::WalkArgs<R, D>& a, int mode, hipStream_t st) {
-  if (a.prog.type == wob::P_VERTEX) launch_walk_vx<R, D, wob::X_VDATA>(a, mode, st);
-  else launch_walk_vx<R, D, wob::X_NONE>(a, mode, st);
+void launch_walk(const wob::WalkArgs<R, D>& a, int mode, int32_t n_cu, hipStream_t st) {
+  if (a.prog.type == wob::P_VERTEX) launch_walk_vx<R, D, wob::X_VDATA>(a, mode, n_cu, st);
+  else launch_walk_vx<R, D, wob::X_NONE>(a, mode, n_cu, st);
 }
 
 wob_status run_walk(wob_scene sc, const void* points, const int32_t* point_prim, int64_t n_points,
@@ -487,7 +507,7 @@ wob_status run_walk(wob_scene sc, const void* points, const int32_t* point_prim,
       a.cv_g0 = cv_g0 ? cv_g0 : cv_g;
       a.anchor_pts = (const float*)anchor_pts;
       a.anchor_prim = anchor_prim;
-      launch_walk<float, 3>(a, mode, st);
+      launch_walk<float, 3>(a, mode, sc->n_cu, st);
     } else {
       auto a = make_args<float, 2>(sc, pl, points, point_prim, n_points, bc, samples, walk_len, seed);
       a.mean_out = (float*)mean_out; a.var_out = (float*)var_out; a.path_out = (float*)path_out;
@@ -496,7 +516,7 @@ wob_status run_walk(wob_scene sc, const void* points, const int32_t* point_prim,
       a.point_ids = point_ids;
       a.anchor_pts = (const float*)anchor_pts;
       a.anchor_prim = anchor_prim;
-      launch_walk<float, 2>(a, mode, st);
+      launch_walk<float, 2>(a, mode, sc->n_cu, st);
     }
   } else {
     if (sc->dim == 3) {
@@ -507,7 +527,7 @@ wob_status run_walk(wob_scene sc, const void* points, const int32_t* point_prim,
       a.point_ids = point_ids;
       a.anchor_pts = (const double*)anchor_pts;
       a.anchor_prim = anchor_prim;
-      launch_walk<double, 3>(a, mode, st);
+      launch_walk<double, 3>(a, mode, sc->n_cu, st);
     } else {
       auto a = make_args<double, 2>(sc, pl, points, point_prim, n_points, bc, samples, walk_len, seed);
       a.mean_out = (double*)mean_out; a.var_out = (double*)var_out; a.path_out = (double*)path_out;
@@ -516,7 +536,7 @@ wob_status run_walk(wob_scene sc, const void* points, const int32_t* point_prim,
       a.point_ids = point_ids;
       a.anchor_pts = (const double*)anchor_pts;
       a.anchor_prim = anchor_prim;
-      launch_walk<double, 2>(a, mode, st);
+      launch_walk<double, 2>(a, mode, sc->n_cu, st);
     }
   }
   return hipGetLastError() == hipSuccess ? WOB_OK : WOB_E_DEVICE;
@@ -593,14 +613,17 @@ wob_status build_scene(int32_t dim, int32_t precision, const double* verts, int6
     else return WOB_E_ARG;
     if (alpha && !std::isfinite(alpha[j])) return WOB_E_ARG;
   }
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return WOB_E_DEVICE;
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu <= 0)
+    return WOB_E_DEVICE;
   wobhost::Bvh bvh = wobhost::build_bvh(dim, boxes, kMaxLeaf);
   wob_scene_s* sc = new (std::nothrow) wob_scene_s();
   if (!sc) return WOB_E_ALLOC;
   sc->dim = dim;
   sc->precision = precision;
   sc->device = dev;
+  sc->n_cu = n_cu;
   sc->n_prims = n_prims;
   sc->n_nodes = (int64_t)bvh.nodes.size();
   sc->n_leaves = bvh.n_leaves;
