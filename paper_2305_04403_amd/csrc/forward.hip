@@ -28,13 +28,20 @@ namespace {
 // a vertex gets a non-finite value (records of ended paths sit far away with
 // strength 0, so they add exactly 0; no per-pair distance test).
 //
-// A workgroup holds 64 * PPL points (PPL per lane) and its four
-// wavefronts split the paths in four contiguous ranges; the vertex records are
-// read at wavefront-uniform addresses (scalar loads, shared by all lanes), so
-// the inner loop is register arithmetic only.  G is accumulated without its
-// constant factor: 3D sum w / rho, 2D sum w log2(rho^2); per path the value is
-// summed in R over chunks of kGatherChunk paths and the chunk sums in binary64.
-constexpr int kGatherPPL = 2;  // points per lane of the launch
+// A workgroup holds 64 / SUB * PPL points: SUB lanes of a wavefront share PPL
+// points each and take the paths in turn, and its WAVES wavefronts split the
+// paths in as many contiguous ranges.  Bound by arithmetic where the chip is
+// full (8 instructions a pair, one of them a reciprocal square root): the split
+// over the paths is what fills it for few points.  50,000 points x 16,384
+// paths of 4 vertices took 1.92 ms with one lane per point, two points per lane,
+// four wavefronts and scalar loads of the vertices (391 workgroups for 256
+// CUs); with 16 lanes per 4 points and 8 wavefronts 0.83 ms, whole call, against
+// 1.43 with 16 wavefronts of the old form and 1.19 with 16 of the new.  At 250,000
+// points, where both fill the chip, 3.66 ms against 3.98: the vertex records
+// come from L1 four points at a time and the old form goes.
+// G is accumulated without its constant factor: 3D sum w / rho, 2D sum
+// w log2(rho^2); per path the value is summed in R over chunks of
+// kGatherChunk of a lane's paths and the chunk sums in binary64.
 constexpr int kGatherChunk = 32;
 
 template <typename R>
@@ -49,35 +56,36 @@ __device__ __forceinline__ R log2_dist2(R r2) {
   else return log2(r2);
 }
 
-template <typename R, int D, int PPL>
-__global__ void __launch_bounds__(256) gather_kernel(const R* __restrict__ vtx, int64_t n_paths, int32_t M,
-                                                     const R* __restrict__ points, int64_t n_points,
-                                                     R* __restrict__ mean_out, R* __restrict__ var_out) {
-  __shared__ double red[4][64 * PPL][2];
-  const int lane = threadIdx.x & 63;
+template <typename R, int D, int PPL, int WAVES, int SUB>
+__global__ void __launch_bounds__(64 * WAVES) gather_kernel(const R* __restrict__ vtx, int64_t n_paths, int32_t M,
+                                                            const R* __restrict__ points, int64_t n_points,
+                                                            R* __restrict__ mean_out, R* __restrict__ var_out) {
+  constexpr int PW = 64 / SUB;  // points per wavefront and q
+  __shared__ double red[WAVES][PW * PPL][2];
+  const int lane = threadIdx.x & 63, place = lane % PW, sub = lane / PW;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t base = (int64_t)blockIdx.x * (64 * PPL);
+  const int64_t base = (int64_t)blockIdx.x * (PW * PPL);
   R px[PPL], py[PPL], pz[PPL];
 #pragma unroll
   for (int q = 0; q < PPL; ++q) {
-    int64_t i = base + lane + 64 * q;
+    int64_t i = base + place + PW * q;
     if (i >= n_points) i = n_points - 1;
     px[q] = points[i * D + 0];
     py[q] = points[i * D + 1];
     pz[q] = D == 3 ? points[i * D + 2] : (R)0;
   }
-  const int64_t per = (n_paths + 3) / 4;
+  const int64_t per = (n_paths + WAVES - 1) / WAVES;
   const int64_t j0 = wave * per < n_paths ? wave * per : n_paths;
   const int64_t j1 = j0 + per < n_paths ? j0 + per : n_paths;
   double S[PPL], Q[PPL];
 #pragma unroll
   for (int q = 0; q < PPL; ++q) S[q] = Q[q] = 0.0;
-  for (int64_t j = j0; j < j1; j += kGatherChunk) {
-    const int64_t je = j + kGatherChunk < j1 ? j + kGatherChunk : j1;
+  for (int64_t j = j0 + sub; j < j1; j += kGatherChunk * SUB) {
+    const int64_t je = j + kGatherChunk * SUB < j1 ? j + kGatherChunk * SUB : j1;
     R s[PPL], s2[PPL];
 #pragma unroll
     for (int q = 0; q < PPL; ++q) s[q] = s2[q] = (R)0;
-    for (int64_t jj = j; jj < je; ++jj) {
+    for (int64_t jj = j; jj < je; jj += SUB) {
       const R* v = vtx + jj * M * 4;
       R c[PPL];
 #pragma unroll
@@ -109,24 +117,33 @@ __global__ void __launch_bounds__(256) gather_kernel(const R* __restrict__ vtx, 
       Q[q] += (double)s2[q];
     }
   }
+  for (int off = PW; off < 64; off *= 2) {  // the lanes that share a point
 #pragma unroll
-  for (int q = 0; q < PPL; ++q) {
-    red[wave][lane + 64 * q][0] = S[q];
-    red[wave][lane + 64 * q][1] = Q[q];
+    for (int q = 0; q < PPL; ++q) {
+      S[q] += __shfl_xor(S[q], off, 64);
+      Q[q] += __shfl_xor(Q[q], off, 64);
+    }
+  }
+  if (sub == 0) {
+#pragma unroll
+    for (int q = 0; q < PPL; ++q) {
+      red[wave][place + PW * q][0] = S[q];
+      red[wave][place + PW * q][1] = Q[q];
+    }
   }
   __syncthreads();
-  if (wave != 0) return;
+  if (wave != 0 || sub != 0) return;
   // G's constant: 3D 1 / (4 pi); 2D -ln 2 / (4 pi) (G = -ln(rho^2) / (4 pi))
   const double kc = D == 3 ? 0.25 / 3.14159265358979323846 : -0.69314718055994530942 * 0.25 / 3.14159265358979323846;
   const double n = (double)n_paths;
 #pragma unroll
   for (int q = 0; q < PPL; ++q) {
-    const int64_t i = base + lane + 64 * q;
+    const int64_t i = base + place + PW * q;
     if (i >= n_points) continue;
     double ts = 0.0, tq = 0.0;
-    for (int w = 0; w < 4; ++w) {
-      ts += red[w][lane + 64 * q][0];
-      tq += red[w][lane + 64 * q][1];
+    for (int w = 0; w < WAVES; ++w) {
+      ts += red[w][place + PW * q][0];
+      tq += red[w][place + PW * q][1];
     }
     const double mean = ts / n;
     mean_out[i] = (R)(kc * mean);
@@ -177,12 +194,15 @@ wob_status launch_paths(const wob_scene_s* sc, const wob_bc* bc, const float* cd
   std::memset(&a, 0, sizeof(a));
   a.scene = view<R, D>(sc);
   a.prog = make_program<R>(sc, bc);
-  // one lane per group of kFwdPathsPerLane paths: forward paths are short
-  // (M - 1 lines from the boundary), so fewer per lane keep enough waves in
-  // flight (2^20 paths of 4 vertices: 2.7 ms with 4 per lane, 4.0 ms with 8)
-  constexpr int kFwdPathsPerLane = 4;
-  a.n_points = (n_paths + kFwdPathsPerLane - 1) / kFwdPathsPerLane;
-  a.N = kFwdPathsPerLane;
+  // One lane per path: the lanes of a wavefront that start together end
+  // together (M - 1 lines from the boundary), and shorter wavefronts wait less
+  // for their slowest lane (16,384 paths of 4 vertices on the 9,216-triangle
+  // tori: 1.12 ms with four paths per lane, 0.15 with one; 1M paths
+  // with 100 points 3.08 against 3.04 ms).  Beyond 2^30 paths four per lane,
+  // within the 2^32 lanes of a launch.
+  const int64_t per_lane = n_paths > ((int64_t)1 << 30) ? 4 : 1;
+  a.n_points = (n_paths + per_lane - 1) / per_lane;
+  a.N = (int32_t)per_lane;
   a.M = walk_len;
   a.L = walk_len - 1;
   a.phi = (R)bc->domain;
@@ -206,13 +226,31 @@ wob_status launch_paths(const wob_scene_s* sc, const wob_bc* bc, const float* cd
   return hipGetLastError() == hipSuccess ? WOB_OK : WOB_E_DEVICE;
 }
 
+template <typename R, int D, int PPL, int WAVES, int SUB>
+void launch_gather_as(const R* vtx, int64_t n_paths, int32_t walk_len, const R* points, int64_t n_points,
+                      R* mean_out, R* var_out, hipStream_t st) {
+  constexpr int64_t per_block = 64 / SUB * PPL;
+  constexpr int64_t per_launch = (int64_t)1 << 26;  // within the 2^32 lanes of a launch
+  for (int64_t p = 0; p < n_points; p += per_launch) {
+    const int64_t n = n_points - p < per_launch ? n_points - p : per_launch;
+    hipLaunchKernelGGL((gather_kernel<R, D, PPL, WAVES, SUB>), dim3((unsigned)((n + per_block - 1) / per_block)),
+                       dim3(64 * WAVES), 0, st, vtx, n_paths, walk_len, points + p * D, n, mean_out + p,
+                       var_out ? var_out + p : nullptr);
+  }
+}
+
+// 128 lanes take a point's paths, 1,024 below 8 points per CU, where the first
+// leaves CUs idle (65,536 paths of 4 vertices: 1,000 points 0.38 ms against
+// 0.69, 2,000 0.52 against 0.68, 4,000 0.78 against 0.68).
 template <typename R, int D>
-wob_status launch_gather(const void* vtx, int64_t n_paths, int32_t walk_len, const void* points,
-                         int64_t n_points, void* mean_out, void* var_out, hipStream_t st) {
-  const int64_t per_block = 64 * kGatherPPL;
-  const dim3 grid((unsigned)((n_points + per_block - 1) / per_block)), block(256);
-  hipLaunchKernelGGL((gather_kernel<R, D, kGatherPPL>), grid, block, 0, st, (const R*)vtx, n_paths, walk_len,
-                     (const R*)points, n_points, (R*)mean_out, (R*)var_out);
+wob_status launch_gather(const wob_scene_s* sc, const void* vtx, int64_t n_paths, int32_t walk_len,
+                         const void* points, int64_t n_points, void* mean_out, void* var_out, hipStream_t st) {
+  if (n_points < (int64_t)sc->n_cu * 8)
+    launch_gather_as<R, D, 4, 16, 64>((const R*)vtx, n_paths, walk_len, (const R*)points, n_points, (R*)mean_out,
+                                      (R*)var_out, st);
+  else
+    launch_gather_as<R, D, 4, 8, 16>((const R*)vtx, n_paths, walk_len, (const R*)points, n_points, (R*)mean_out,
+                                     (R*)var_out, st);
   return hipGetLastError() == hipSuccess ? WOB_OK : WOB_E_DEVICE;
 }
 
@@ -339,10 +377,10 @@ wob_status wob_forward_gather(wob_scene sc, const void* vtx, int64_t n_paths, in
   if (!on_device(sc->device)) return WOB_E_DEVICE;
   hipStream_t st = (hipStream_t)stream;
   if (sc->precision == WOB_F32)
-    return sc->dim == 3 ? launch_gather<float, 3>(vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st)
-                        : launch_gather<float, 2>(vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st);
-  return sc->dim == 3 ? launch_gather<double, 3>(vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st)
-                      : launch_gather<double, 2>(vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st);
+    return sc->dim == 3 ? launch_gather<float, 3>(sc, vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st)
+                        : launch_gather<float, 2>(sc, vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st);
+  return sc->dim == 3 ? launch_gather<double, 3>(sc, vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st)
+                      : launch_gather<double, 2>(sc, vtx, n_paths, walk_len, points, n_points, mean_out, var_out, st);
 }
 
 }  // extern "C"
