@@ -1362,122 +1362,210 @@ walk_kernel(WalkArgs<R, D> a) {
 //   h = hash32(id + 0x9e3779b9 (seed_lo + 1)),
 //   u0 = unit(hash32(h ^ 0x68e31da4)), u1 = unit(hash32(h ^ 0xb5297a4d)),
 //   reflected into the triangle when u0 + u1 > 1, y_T = v0 + u0 e1 + u1 e2.
-// Every workgroup streams the triangles through LDS in tiles of 256; a far pair
-// costs one distance test and one reciprocal square root.  Each lane keeps 4
-// points in registers.  A tile whose triangles all have g_T = 0 adds exactly
-// zero: its pairs are skipped (the whole sum, for g = 0).
+//
+// Bound by arithmetic where the chip is full: a far pair is ten instructions,
+// one of them a reciprocal square root.  A wavefront takes 64 / SUB * PPT points:
+// SUB lanes share PPT points each and take the triangles in turn from LDS tiles of
+// kAddTile that the workgroup's wavefronts share.  What decides for the rare near
+// pair must not cost the far ones: near needs |x - y_T| < 4 r + |y_T - c|, a bound
+// kept beside y_T; pairs within it go to a queue, and 64 of them at a time take
+// the exact centroid test and the closed form, each on a lane of its own (a
+// near pair in a wavefront's step cost all 64 lanes the closed form).  100,000
+// points x 60,976 triangles: 32 ms with four points per lane of 98 workgroups of
+// 1,024 points and the centroid test at every pair, 2.6 so (2.3e12 pairs/s; the
+// kernel's arithmetic alone allows about 4.7e12); 200,000 points 4.55, and 1.24 times
+// that with the general root at far pairs.  Tiles whose triangles all have
+// g_T = 0 add exactly zero and are skipped (the whole sum, for g = 0).
+constexpr int kAddTile = 512, kAddWaves = 8, kAddQueue = 128;
+
 template <typename R>
-__global__ void __launch_bounds__(256) cv_addback_kernel(SceneView<R, 3> s, const R* __restrict__ g_by_id,
-                                                         const R* __restrict__ points, int64_t n,
-                                                         uint32_t seed, R* out, int accumulate) {
-  // per triangle: [c (3), (4 r)^2] [y_T (3), g A / (4 pi)] [v (9), t (9), u (9), n (3), g, pad]
-  // (the pad words of the first four records carry the wavefronts' votes)
-  constexpr int TILE = 256, PPT = 4, NF = 40;
-  __shared__ __align__(16) R tile[TILE * NF];
-  const int tid = threadIdx.x;
-  R x[PPT][3], acc[PPT];
-  int64_t pidx[PPT];
+__device__ __forceinline__ R far_rsqrt(R r2) {
+  if constexpr (sizeof(R) == 4) return __builtin_amdgcn_rsqf(r2);  // r2 is no denormal: see kAddReach
+  else return rsqrt_<R>(r2);
+}
+// least squared reach of a triangle's queue test: what is nearer to y_T takes the
+// general root
+constexpr float kAddReach = 1e-30f;
+
+// The far record of triangle j: a fixed uniform point y_T on it and the weight
+// g_T A_T / (4 pi); near2 the near test's (4 r)^2 and cen its centre.
+template <typename R>
+__device__ __forceinline__ void addback_far(const PrimGeo<R>& g, R gT, uint32_t seed, R cen[3], R& near2, R y[3],
+                                            R& gw) {
+  R v[3][3], rad2 = 0;
+  for (int k = 0; k < 3; ++k) {
+    v[0][k] = g.v0[k];
+    v[1][k] = g.v0[k] + g.e1[k];
+    v[2][k] = g.v0[k] + g.e2[k];
+  }
+  for (int k = 0; k < 3; ++k) cen[k] = (v[0][k] + v[1][k] + v[2][k]) / (R)3;
+  for (int c = 0; c < 3; ++c) {
+    const R dc[3] = {v[c][0] - cen[0], v[c][1] - cen[1], v[c][2] - cen[2]};
+    rad2 = fmax(rad2, dot3(dc, dc));
+  }
+  near2 = (R)16 * rad2;
+  const uint32_t h = hash32((uint32_t)g.id + 0x9e3779b9u * (seed + 1u));
+  R a = unit<R>(hash32(h ^ 0x68e31da4u)), b = unit<R>(hash32(h ^ 0xb5297a4du));
+  if (a + b > (R)1) {
+    a = (R)1 - a;
+    b = (R)1 - b;
+  }
+  for (int k = 0; k < 3; ++k) y[k] = v[0][k] + a * (v[1][k] - v[0][k]) + b * (v[2][k] - v[0][k]);
+  R cr[3];
+  cross3(g.e1, g.e2, cr);
+  gw = gT * (R)0.5 * sqrt(dot3(cr, cr)) * (R)(0.25 / 3.14159265358979323846);
+}
+
+// One queued pair: the exact test, then the closed form or the far value.
+template <typename R>
+__device__ __forceinline__ R addback_pair(const SceneView<R, 3>& s, const R* g_by_id, int32_t j, uint32_t seed,
+                                          const R x[3]) {
+  const PrimGeo<R> g = load_prim<R, 3>(s, j);
+  const R gT = g_by_id[g.id];
+  R cen[3], near2, y[3], gw;
+  addback_far<R>(g, gT, seed, cen, near2, y, gw);
+  const R dx = x[0] - cen[0], dy = x[1] - cen[1], dz = x[2] - cen[2];
+  if (!(dx * dx + dy * dy + dz * dz < near2)) {
+    const R yx = y[0] - x[0], yy = y[1] - x[1], yz = y[2] - x[2];
+    return gw * rsqrt_<R>(yx * yx + yy * yy + yz * yz);
+  }
+  R v[3][3], tt[3][3], uu[3][3], nn[3];
+  load_normal<R, 3>(s, j, nn);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    v[0][k] = g.v0[k];
+    v[1][k] = g.v0[k] + g.e1[k];
+    v[2][k] = g.v0[k] + g.e2[k];
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int c1 = c == 2 ? 0 : c + 1;
+    const R e[3] = {v[c1][0] - v[c][0], v[c1][1] - v[c][1], v[c1][2] - v[c][2]};
+    const R il = rsqrt_<R>(dot3(e, e));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tt[c][k] = e[k] * il;
+    cross3(tt[c], nn, uu[c]);
+  }
+  return gT * tri_potential<R>(v, tt, uu, nn, x);
+}
+
+template <typename R, int SUB, int PPT>
+__global__ void __launch_bounds__(64 * kAddWaves) cv_addback_kernel(SceneView<R, 3> s, const R* __restrict__ g_by_id,
+                                                                    const R* __restrict__ points, int64_t n,
+                                                                    uint32_t seed, R* out, int accumulate) {
+  constexpr int PW = 64 / SUB, PPW = PW * PPT;  // points per wavefront: at most 64
+  static_assert(PPW <= 64, "a lane per point for the queued sums");
+  struct alignas(4 * sizeof(R)) Far { R y[3], gw; };
+  __shared__ Far far_rec[kAddTile];
+  __shared__ R reach2[kAddTile];
+  __shared__ int32_t q_prim[kAddWaves][kAddQueue], q_point[kAddWaves][kAddQueue];
+  __shared__ int32_t vote[2][kAddWaves];
+  const int tid = threadIdx.x, lane = tid & 63, place = lane % PW, sub = lane / PW;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t base = ((int64_t)blockIdx.x * kAddWaves + wave) * PPW;
+  R x[PPT][3], acc[PPT], queued = 0;  // queued: of point `lane` of the wavefront
+  int held = 0;
 #pragma unroll
   for (int k = 0; k < PPT; ++k) {
-    pidx[k] = ((int64_t)blockIdx.x * PPT + k) * 256 + tid;
-    const int64_t q = pidx[k] < n ? pidx[k] : 0;
+    const int64_t p = base + place + PW * k, q = p < n ? p : 0;
     x[k][0] = points[q * 3 + 0];
     x[k][1] = points[q * 3 + 1];
     x[k][2] = points[q * 3 + 2];
     acc[k] = 0;
   }
-  for (int32_t t0 = 0; t0 < s.n_prims; t0 += TILE) {
+  // the first m entries of the wavefront's queue, added in order
+  auto flush = [&](int m) {
+    __builtin_amdgcn_wave_barrier();
+    int pt = 0;
+    R v = 0;
+    if (lane < m) {
+      pt = q_point[wave][lane];
+      const int64_t p = base + pt, q = p < n ? p : 0;
+      const R xq[3] = {points[q * 3 + 0], points[q * 3 + 1], points[q * 3 + 2]};
+      v = addback_pair<R>(s, g_by_id, q_prim[wave][lane], seed, xq);
+    }
+    for (int e = 0; e < m; ++e) {
+      const int pe = __shfl(pt, e, 64);
+      const R ve = __shfl(v, e, 64);
+      if (pe == lane) queued += ve;
+    }
+    // the entries past the first 64 move to the front
+    if (lane < held - m) {
+      q_prim[wave][lane] = q_prim[wave][m + lane];
+      q_point[wave][lane] = q_point[wave][m + lane];
+    }
+    held -= m;
+    __builtin_amdgcn_wave_barrier();
+  };
+  int parity = 0;
+  for (int32_t t0 = 0; t0 < s.n_prims; t0 += kAddTile, parity ^= 1) {
     __syncthreads();
     const int32_t j = t0 + tid;
-    R* T = tile + tid * NF;
+    Far f = {{(R)0, (R)0, (R)0}, (R)0};
+    R reach = -1;  // past the last triangle: taken as far, with no weight
     bool nonzero = false;
     if (j < s.n_prims) {
       const PrimGeo<R> g = load_prim<R, 3>(s, j);
-      R nn[3];
-      load_normal<R, 3>(s, j, nn);
-      R v[3][3];
-      for (int k = 0; k < 3; ++k) {
-        v[0][k] = g.v0[k];
-        v[1][k] = g.v0[k] + g.e1[k];
-        v[2][k] = g.v0[k] + g.e2[k];
-      }
-      R cen[3], rad2 = 0;
-      for (int k = 0; k < 3; ++k) cen[k] = (v[0][k] + v[1][k] + v[2][k]) / (R)3;
-      for (int c = 0; c < 3; ++c) {
-        const int c1 = c == 2 ? 0 : c + 1;
-        R e[3] = {v[c1][0] - v[c][0], v[c1][1] - v[c][1], v[c1][2] - v[c][2]};
-        const R il = rsqrt_<R>(dot3(e, e));
-        R tt[3] = {e[0] * il, e[1] * il, e[2] * il}, uu[3];
-        cross3(tt, nn, uu);
-        R dc[3] = {v[c][0] - cen[0], v[c][1] - cen[1], v[c][2] - cen[2]};
-        rad2 = fmax(rad2, dot3(dc, dc));
-        for (int k = 0; k < 3; ++k) {
-          T[8 + c * 3 + k] = v[c][k];
-          T[17 + c * 3 + k] = tt[k];
-          T[26 + c * 3 + k] = uu[k];
-        }
-      }
-      R cr[3];
-      cross3(g.e1, g.e2, cr);
       const R gT = g_by_id[g.id];
       nonzero = gT != (R)0;
-      const uint32_t h = hash32((uint32_t)g.id + 0x9e3779b9u * (seed + 1u));
-      R a = unit<R>(hash32(h ^ 0x68e31da4u)), b = unit<R>(hash32(h ^ 0xb5297a4du));
-      if (a + b > (R)1) {
-        a = (R)1 - a;
-        b = (R)1 - b;
-      }
-      T[0] = cen[0];
-      T[1] = cen[1];
-      T[2] = cen[2];
-      T[3] = (R)16 * rad2;  // (4 r)^2
-      for (int k = 0; k < 3; ++k) T[4 + k] = v[0][k] + a * (v[1][k] - v[0][k]) + b * (v[2][k] - v[0][k]);
-      T[7] = gT * (R)0.5 * sqrt(dot3(cr, cr)) * (R)(0.25 / 3.14159265358979323846);
-      T[35] = nn[0];
-      T[36] = nn[1];
-      T[37] = nn[2];
-      T[38] = gT;
+      R cen[3], near2;
+      addback_far<R>(g, gT, seed, cen, near2, f.y, f.gw);
+      const R d[3] = {f.y[0] - cen[0], f.y[1] - cen[1], f.y[2] - cen[2]};
+      reach = sqrt(near2) + sqrt(dot3(d, d));
+      reach = reach * reach * (R)1.0001;  // well over what the two tests' rounding can differ by
+      if (reach < (R)kAddReach) reach = (R)kAddReach;
     }
-    // whether any g_T of the tile is non-zero: each wavefront's vote in the
-    // pad word of one of the first four records (no LDS beyond the tile's
-    // 40 KiB, which lets four workgroups share a CU)
+    far_rec[tid] = f;
+    reach2[tid] = reach;
     const bool wave_nonzero = __ballot(nonzero) != 0;  // every lane of the wavefront votes
-    if ((tid & 63) == 0) tile[(tid >> 6) * NF + 39] = wave_nonzero ? (R)1 : (R)0;
+    if (lane == 0) vote[parity][wave] = wave_nonzero;
     __syncthreads();
-    if (tile[39] == (R)0 && tile[NF + 39] == (R)0 && tile[2 * NF + 39] == (R)0 && tile[3 * NF + 39] == (R)0)
-      continue;  // the same decision in every lane
-    const int cnt = s.n_prims - t0 < TILE ? s.n_prims - t0 : TILE;
-    for (int q = 0; q < cnt; ++q) {
-      const R* P = tile + q * NF;
-      const R c0 = P[0], c1 = P[1], c2 = P[2], near2 = P[3];
-      const R y0 = P[4], y1 = P[5], y2 = P[6], gw = P[7];
+    int any = 0;
+    for (int w = 0; w < kAddWaves; ++w) any |= vote[parity][w];
+    if (!any) continue;  // the same decision in every lane
+    const int cnt = s.n_prims - t0 < kAddTile ? s.n_prims - t0 : kAddTile;
+    for (int q = sub; q - sub < cnt; q += SUB) {
+      const Far t = far_rec[q];
+      const R lim = reach2[q];
+      bool close = false;
+      R d2[PPT];
 #pragma unroll
       for (int k = 0; k < PPT; ++k) {
-        const R dx = x[k][0] - c0, dy = x[k][1] - c1, dz = x[k][2] - c2;
-        if (dx * dx + dy * dy + dz * dz < near2) {
-          R v[3][3], tt[3][3], uu[3][3], nn[3];
+        const R yx = t.y[0] - x[k][0], yy = t.y[1] - x[k][1], yz = t.y[2] - x[k][2];
+        d2[k] = yx * yx + yy * yy + yz * yz;
+        close = close || d2[k] < lim;
+      }
+      if (__ballot(close) == 0) {
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
+        for (int k = 0; k < PPT; ++k) acc[k] += t.gw * far_rsqrt<R>(d2[k]);
+        continue;
+      }
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-              v[c][m] = P[8 + c * 3 + m];
-              tt[c][m] = P[17 + c * 3 + m];
-              uu[c][m] = P[26 + c * 3 + m];
-            }
-          nn[0] = P[35];
-          nn[1] = P[36];
-          nn[2] = P[37];
-          acc[k] += P[38] * tri_potential<R>(v, tt, uu, nn, x[k]);
-        } else {
-          const R yx = y0 - x[k][0], yy = y1 - x[k][1], yz = y2 - x[k][2];
-          acc[k] += gw * rsqrt_<R>(yx * yx + yy * yy + yz * yz);
+      for (int k = 0; k < PPT; ++k) {
+        const bool c = d2[k] < lim;
+        if (!c) acc[k] += t.gw * far_rsqrt<R>(d2[k]);
+        const uint64_t mask = __ballot(c);
+        if (mask == 0) continue;
+        if (c) {
+          const int e = held + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+          q_prim[wave][e] = t0 + q;
+          q_point[wave][e] = place + PW * k;
         }
+        held += __popcll(mask);
+        if (held >= 64) flush(64);
       }
     }
   }
+  if (held > 0) flush(held);
 #pragma unroll
-  for (int k = 0; k < PPT; ++k)
-    if (pidx[k] < n) out[pidx[k]] = accumulate ? out[pidx[k]] + acc[k] : acc[k];
+  for (int k = 0; k < PPT; ++k) {
+    R sum = acc[k];
+    for (int off = PW; off < 64; off *= 2) sum += __shfl_xor(sum, off, 64);
+    sum += __shfl(queued, place + PW * k, 64);
+    const int64_t p = base + place + PW * k;
+    if (sub == 0 && p < n) out[p] = accumulate ? out[p] + sum : sum;
+  }
 }
 
 // g0[id] = (g ? g[id] : 0) + 2 phi s(centroid of id): the line-0 table of the
