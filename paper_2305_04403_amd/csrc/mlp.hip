@@ -24,7 +24,8 @@ constexpr int F0 = 2 * KF;    // features
 constexpr int HD = 128;       // hidden width
 constexpr int NL = 4;         // hidden layers
 constexpr int TR = 64;        // rows per workgroup
-constexpr int NT = 256;       // threads per workgroup (4 wavefronts)
+constexpr int NT = 256;       // threads per workgroup of the forward pass (4 wavefronts)
+constexpr int GT = 1024;      // threads per workgroup of the backward pass (16 wavefronts)
 constexpr int kFwdGrid = 1024;  // forward-pass workgroups (256 CUs x 4)
 
 // parameter offsets (floats): W_l [out][in] then b_l, layers 0..NL (NL = output)
@@ -34,8 +35,10 @@ constexpr int offW(int l) { return l == 0 ? 0 : offW(l - 1) + out_of(l - 1) * in
 constexpr int offB(int l) { return offW(l) + out_of(l) * in_of(l); }
 constexpr int NP = offB(NL) + 1;
 static_assert(NP == 53889, "parameter count");
+constexpr int NPP = (NP + 3) / 4 * 4;  // floats per partial gradient (16-byte aligned)
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 
 struct Net {
@@ -77,52 +80,42 @@ __device__ __forceinline__ float silu_grad(float s) {
 
 // MFMA 16x16x32 operand fragments.  Lane l holds rows/cols (l % 16) and the
 // eight k values 8 (l / 16) .. +7; the accumulator holds rows 4 (l / 16) + v.
-__device__ __forceinline__ bf16x8 frag_rows(const __bf16* a, int ld, int row, int k0) {
-  // a[row][k0 .. k0 + 7], contiguous
-  bf16x8 f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = a[row * ld + k0 + e];
-  return f;
-}
-__device__ __forceinline__ bf16x8 frag_cols(const __bf16* a, int ld, int k0, int col) {
-  // a[k0 .. k0 + 7][col], strided
-  bf16x8 f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f[e] = a[(k0 + e) * ld + col];
-  return f;
-}
 __device__ __forceinline__ floatx4 mfma(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Shared memory of one workgroup.
-struct Smem {
-  __bf16 a0[TR * F0];
-  __bf16 act[NL][TR * HD];  // activations h_1 .. h_4 (bfloat16)
-  __bf16 dq[TR * HD];       // bfloat16 pre-activation gradient of the current layer
-  float ds[TR * HD];        // binary32 pre-activation gradient
-  float g5[TR];
-  float red[NT];
-};
-
 // The forward pass alone: two activation buffers (layer l writes buffer l % 2)
 // whose rows are padded by 8 elements, so that the 16 rows of an operand
 // fragment start 16 bytes apart and spread over the LDS banks.  About 40 KiB.
-constexpr int LDA0 = F0 + 8, LDH = HD + 8;
+constexpr int LDA0 = F0 + 8, LDH = HD + 8, LDT = TR + 8;
 struct FwdSmem {
   __bf16 a0[TR * LDA0];
   __bf16 act[2][TR * LDH];
   float w5[HD];  // the output layer's weights (their bfloat16 values)
 };
 
-// Features and the four hidden layers for rows r0 .. r0 + 63 into LDS (the
-// backward pass): the features to a0, layer l's activations to act + l TR HD.
-// Pre-activations go to `sbuf` (4 x 64 x 128 floats) when it is not null.
-// Returns the last layer's buffer.
+// The backward pass.  The weight gradients contract over the rows, so what enters
+// them lies transposed too ([column][row], rows of LDT): every operand
+// fragment of either product is 16 contiguous bytes.  `row` holds the
+// activations in turn and then the gradients dq, `dqt` dq transposed: two buffers
+// each, so that a layer needs one barrier.  About 140 KiB.
+struct GradSmem {
+  __bf16 row[2][TR * LDH];
+  __bf16 a0[TR * LDA0];
+  __bf16 a0t[F0 * LDT];
+  __bf16 at[NL - 1][HD * LDT];
+  __bf16 dqt[2][HD * LDT];
+  float outp[HD / 16][TR];  // the output layer's partial sums per column block
+  float half[3][HD];        // column sums of rows 32 .. 63 (two layers in turn, the output layer)
+  float g5[TR];
+};
+
 // The Fourier features of rows r0 .. r0 + 63 into a0 (row stride lda; rows
-// past n are zero).
-__device__ void features_tile(const Net& net, const float* y, int64_t n, int64_t r0, __bf16* a0, int lda) {
-  for (int idx = threadIdx.x; idx < TR * KF; idx += NT) {
+// past n are zero), by T threads; transposed to a0t as well when it is not null.
+template <int T>
+__device__ void features_tile(const Net& net, const float* y, int64_t n, int64_t r0, __bf16* a0, int lda,
+                              __bf16* a0t = nullptr) {
+  for (int idx = threadIdx.x; idx < TR * KF; idx += T) {
     const int r = idx / KF, k = idx % KF;
     const int64_t row = r0 + r;
     float sv = 0.f, cv = 0.f;
@@ -141,63 +134,11 @@ __device__ void features_tile(const Net& net, const float* y, int64_t n, int64_t
     }
     a0[r * lda + k] = (__bf16)sv;
     a0[r * lda + KF + k] = (__bf16)cv;
-  }
-}
-
-template <bool ALL>
-__device__ const __bf16* forward_tile(const Net& net, const float* y, int64_t n, int64_t r0,
-                                      __bf16* a0, __bf16* act, float* sbuf) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  features_tile(net, y, n, r0, a0, F0);
-  __syncthreads();
-  for (int l = 0; l < NL; ++l) {
-    const int K = in_of(l);
-    const __bf16* A = l == 0 ? a0 : act + (ALL ? l - 1 : (l - 1) & 1) * TR * HD;
-    __bf16* O = act + (ALL ? l : l & 1) * TR * HD;
-    const __bf16* W = net.wq + offW(l);
-    const int ldw = K;
-    const float* b = net.p + offB(l);
-    floatx4 acc[8];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int row = wave * 16 + (lane & 15);
-    for (int k0 = 0; k0 < K; k0 += 32) {
-      const bf16x8 af = frag_rows(A, K, row, k0 + 8 * (lane >> 4));
-#pragma unroll
-      for (int cb = 0; cb < 8; ++cb) {
-        // B[k][o] = W[o][k]: eight consecutive k of row o of W
-        const int o = cb * 16 + (lane & 15);
-        const bf16x8 bf = *(const bf16x8*)(W + o * ldw + k0 + 8 * (lane >> 4));
-        acc[cb] = mfma(af, bf, acc[cb]);
-      }
+    if (a0t) {
+      a0t[k * LDT + r] = (__bf16)sv;
+      a0t[(KF + k) * LDT + r] = (__bf16)cv;
     }
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-      const int col = cb * 16 + (lane & 15);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int r = wave * 16 + 4 * (lane >> 4) + v;
-        const float s = acc[cb][v] + b[col];
-        if (sbuf) sbuf[(l * TR + r) * HD + col] = s;
-        O[r * HD + col] = (__bf16)silu_rounded(s);
-      }
-    }
-    __syncthreads();
   }
-  return act + (ALL ? NL - 1 : (NL - 1) & 1) * TR * HD;
-}
-
-// Output layer f = W5 . h4 + b5 for the 64 rows; 4 lanes per row.
-__device__ float output_row(const Net& net, const __bf16* h4, int& r_out) {
-  const int tid = threadIdx.x;
-  const int r = tid >> 2, part = tid & 3;
-  float acc = 0.f;
-  for (int i = part * 32; i < part * 32 + 32; ++i)
-    acc += (float)net.wq[offW(NL) + i] * (float)h4[r * HD + i];
-  acc += __shfl_xor(acc, 1, 64);
-  acc += __shfl_xor(acc, 2, 64);
-  r_out = r;
-  return acc + net.p[offB(NL)];
 }
 
 // Forward pass, weight-stationary: wavefront w computes output columns
@@ -234,7 +175,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) ml
   const int64_t n_tiles = (n + TR - 1) / TR;
   for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
     const int64_t r0 = t * TR;
-    features_tile(net, y, n, r0, sm.a0, LDA0);
+    features_tile<NT>(net, y, n, r0, sm.a0, LDA0);
     __syncthreads();
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
@@ -268,8 +209,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) ml
         }
       __syncthreads();
     }
-    // output layer, as output_row computes it (4 lanes per row, 32 terms each
-    // in order, then two butterfly steps), with the weights from LDS
+    // output layer: 4 lanes per row, 32 terms each in order, then two butterfly
+    // steps, with the weights from LDS
     {
       const int r = tid >> 2, part = tid & 3;
       const __bf16* h4 = sm.act[(NL - 1) & 1] + r * LDH;
@@ -291,164 +232,201 @@ struct TargetMap {
 
 // Loss and gradient of one tile: writes the tile's partial gradient (NP floats)
 // and partial loss (sum of squared errors).  scale = 1 / (rows in the batch).
-__global__ void __launch_bounds__(NT) mlp_grad_kernel(Net net, const float* y, const float* target,
+//
+// A chain of small products with a barrier after each: latency bounds it, so the
+// tile has all 16 wavefronts of a CU.  Wavefront w takes columns 16 (w % 8) .. + 15 and
+// rows 32 (w / 8) .. + 31 of every 64 x 128 array, forward and backward alike, so
+// the pre-activations and the binary32 gradients of a lane's eight elements per
+// layer stay in its registers; its weights are loaded ahead of the layer that
+// needs them.  16,384 rows (256 tiles): 94 us with four wavefronts,
+// 16-bit reads of the transposed operands and the pre-activations in memory; a
+// training step of them, all launches, 133 -> 47 us.
+__global__ void __launch_bounds__(GT) mlp_grad_kernel(Net net, const float* y, const float* target,
                                                       TargetMap tm, int64_t n, float scale,
-                                                      float* part_grad, float* part_loss,
-                                                      float* sbuf_all) {
+                                                      float* part_grad, float* part_loss) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  Smem& sm = *reinterpret_cast<Smem*>(smem_raw);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  GradSmem& sm = *reinterpret_cast<GradSmem*>(smem_raw);
+  const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15, lg = lane >> 4, kq = 8 * lg;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), cb = wave & 7, rh = wave >> 3;
+  const int col = 16 * cb + lc;
   const int64_t r0 = (int64_t)blockIdx.x * TR;
-  float* sbuf = sbuf_all + (int64_t)blockIdx.x * NL * TR * HD;
-  float* G = part_grad + (int64_t)blockIdx.x * NP;
-  const __bf16* h4 = forward_tile<true>(net, y, n, r0, sm.a0, sm.act[0], sbuf);
-  int r;
-  const float f = output_row(net, h4, r);
-  float e = 0.f;
-  if (r0 + r < n) {
-    float tv = target[r0 + r];
-    // a non-finite target (a boundary point whose every path was non-finite)
-    // has no weight in the loss: e = 0 (clamping would turn NaN into -clip)
-    if (isfinite(tv)) {
-      if (tm.on) {
-        tv = (tv - tm.shift) * tm.inv_scale;
-        if (tm.clip > 0.f) tv = fminf(fmaxf(tv, -tm.clip), tm.clip);
+  float* G = part_grad + (int64_t)blockIdx.x * NPP;
+  // weight fragments: B[k][o] = W[o][k], o = col
+  const bf16x8 w0 = *(const bf16x8*)(net.wq + offW(0) + col * F0 + kq);
+  bf16x8 wh[NL - 1][HD / 32];
+#pragma unroll
+  for (int l = 1; l < NL; ++l)
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks) wh[l - 1][ks] = *(const bf16x8*)(net.wq + offW(l) + col * HD + 32 * ks + kq);
+  float bias[NL];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) bias[l] = net.p[offB(l) + col];
+  const float w5 = (float)net.wq[offW(NL) + col];
+  features_tile<GT>(net, y, n, r0, sm.a0, LDA0, sm.a0t);
+  __syncthreads();
+
+  // element (j, v) of the lane: row 32 rh + 16 j + 4 lg + v, column col
+  const int rj[2] = {32 * rh + 4 * lg, 32 * rh + 16 + 4 * lg};
+  float s[NL][2][4], h4[2][4];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const __bf16* A = l == 0 ? sm.a0 : sm.row[(l - 1) & 1];
+    const int lda = l == 0 ? LDA0 : LDH;
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < in_of(l) / 32; ++ks)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 af = *(const bf16x8*)(A + (32 * rh + 16 * j + lc) * lda + 32 * ks + kq);
+        acc[j] = mfma(af, l == 0 ? w0 : wh[l == 0 ? 0 : l - 1][ks], acc[j]);
       }
-      e = f - tv;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bf16x4 h;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        s[l][j][v] = acc[j][v] + bias[l];
+        h[v] = (__bf16)silu_rounded(s[l][j][v]);
+        if (l < NL - 1) sm.row[l & 1][(rj[j] + v) * LDH + col] = h[v];
+        else h4[j][v] = (float)h[v];
+      }
+      if (l < NL - 1) *(bf16x4*)(sm.at[l < NL - 1 ? l : 0] + col * LDT + rj[j]) = h;
+    }
+    if (l < NL - 1) __syncthreads();
+  }
+
+  // output layer f = W5 . h4 + b5: 16 columns by butterfly, the column blocks in order
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float f = w5 * h4[j][v];
+#pragma unroll
+      for (int off = 1; off < 16; off *= 2) f += __shfl_xor(f, off, 64);
+      if (lc == 0) sm.outp[cb][rj[j] + v] = f;
+    }
+  __syncthreads();
+  if (wave == 0) {
+    float f = 0.f;
+#pragma unroll
+    for (int c = 0; c < HD / 16; ++c) f += sm.outp[c][lane];
+    f += net.p[offB(NL)];
+    float e = 0.f;
+    if (r0 + lane < n) {
+      float tv = target[r0 + lane];
+      // a non-finite target (a boundary point whose every path was non-finite)
+      // has no weight in the loss: e = 0 (clamping would turn NaN into -clip)
+      if (isfinite(tv)) {
+        if (tm.on) {
+          tv = (tv - tm.shift) * tm.inv_scale;
+          if (tm.clip > 0.f) tv = fminf(fmaxf(tv, -tm.clip), tm.clip);
+        }
+        e = f - tv;
+      }
+    }
+    const float g = 2.f * e * scale;
+    sm.g5[lane] = g;
+    float se = e * e, sg = g;  // the tile's loss and db5
+#pragma unroll
+    for (int off = 1; off < 64; off *= 2) {
+      se += __shfl_xor(se, off, 64);
+      sg += __shfl_xor(sg, off, 64);
+    }
+    if (lane == 0) {
+      part_loss[blockIdx.x] = se;
+      G[offB(NL)] = sg;
     }
   }
-  if ((tid & 3) == 0) sm.g5[r] = 2.f * e * scale;
-  sm.red[tid] = (tid & 3) == 0 ? e * e : 0.f;
-  __syncthreads();
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (tid < s) sm.red[tid] += sm.red[tid + s];
-    __syncthreads();
-  }
-  if (tid == 0) part_loss[blockIdx.x] = sm.red[0];
-
-  // output layer: dW5[i] = sum_r g5 h4[r][i]; db5 = sum_r g5; dh4 = g5 W5q
-  if (tid < HD) {
-    float acc = 0.f;
-    for (int rr = 0; rr < TR; ++rr) acc += sm.g5[rr] * (float)sm.act[NL - 1][rr * HD + tid];
-    G[offW(NL) + tid] = acc;
-  }
-  if (tid == HD) {
-    float acc = 0.f;
-    for (int rr = 0; rr < TR; ++rr) acc += sm.g5[rr];
-    G[offB(NL)] = acc;
-  }
-  // ds for the last hidden layer: dh4 * silu'(s4)
-  for (int idx = tid; idx < TR * HD; idx += NT) {
-    const int rr = idx / HD, o = idx % HD;
-    const float dh = sm.g5[rr] * (float)net.wq[offW(NL) + o];
-    sm.ds[idx] = dh * silu_grad(sbuf[((NL - 1) * TR + rr) * HD + o]);
-  }
   __syncthreads();
 
+  // dW5[i] = sum_r g5 h4[r][i]; ds of the last hidden layer: g5 W5 silu'(s4)
+  float ds[2][4], t5 = 0.f;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float g = sm.g5[rj[j] + v];
+      t5 += g * h4[j][v];
+      ds[j][v] = g * w5 * silu_grad(s[NL - 1][j][v]);
+    }
+  t5 += __shfl_xor(t5, 16, 64);
+  t5 += __shfl_xor(t5, 32, 64);
+  if (rh == 1 && lg == 0) sm.half[2][col] = t5;
+
+#pragma unroll
   for (int l = NL - 1; l >= 0; --l) {
     const int K = in_of(l);  // input width of layer l
-    // bfloat16 copy of ds for the products; bias gradient from binary32 ds
-    for (int idx = tid; idx < TR * HD; idx += NT) sm.dq[idx] = (__bf16)sm.ds[idx];
-    if (tid < HD) {
-      float acc = 0.f;
-      for (int rr = 0; rr < TR; ++rr) acc += sm.ds[rr * HD + tid];
-      G[offB(l) + tid] = acc;
-    }
-    __syncthreads();
-    // dW_l[o][i] = sum_r dq[r][o] a_{l-1}[r][i]: (HD x TR) x (TR x K)
-    {
-      const __bf16* A = l == 0 ? sm.a0 : sm.act[l - 1];
-      const int tiles_i = K / 16, n_tiles = 8 * tiles_i;
-      for (int t = wave; t < n_tiles; t += 4) {
-        const int ob = t / tiles_i, ib = t % tiles_i;
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int k0 = 0; k0 < TR; k0 += 32) {
-          const int kk = k0 + 8 * (lane >> 4);
-          const bf16x8 af = frag_cols(sm.dq, HD, kk, ob * 16 + (lane & 15));  // A[o][r] = dq[r][o]
-          const bf16x8 bf = frag_cols(A, K, kk, ib * 16 + (lane & 15));        // B[r][i] = a[r][i]
-          acc = mfma(af, bf, acc);
-        }
+    // dh's weights: B[o][i] = W[o][i], i = col, from the transposed copy
+    bf16x8 wt[HD / 32];
+    if (l > 0) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int o = ob * 16 + 4 * (lane >> 4) + v, i = ib * 16 + (lane & 15);
-          G[offW(l) + o * K + i] = acc[v];
-        }
+      for (int ks = 0; ks < HD / 32; ++ks) wt[ks] = *(const bf16x8*)(net.wt + offW(l) + col * HD + 32 * ks + kq);
+    }
+    // bfloat16 copy of ds for the products; bias gradient from binary32 ds
+    __bf16* const dq = sm.row[l & 1];
+    __bf16* const dqt = sm.dqt[l & 1];
+    float tb = 0.f;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bf16x4 q;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        q[v] = (__bf16)ds[j][v];
+        if (l > 0) dq[(rj[j] + v) * LDH + col] = q[v];
+        tb += ds[j][v];
+      }
+      *(bf16x4*)(dqt + col * LDT + rj[j]) = q;
+    }
+    tb += __shfl_xor(tb, 16, 64);
+    tb += __shfl_xor(tb, 32, 64);
+    if (rh == 1 && lg == 0) sm.half[l & 1][col] = tb;
+    __syncthreads();
+    if (rh == 0 && lg == 0) {
+      G[offB(l) + col] = tb + sm.half[l & 1][col];
+      if (l == NL - 1) G[offW(NL) + col] = t5 + sm.half[2][col];
+    }
+    // dW_l[o][i] = sum_r a_{l-1}[r][i] dq[r][o]: the lane holds four consecutive
+    // i of one o; this wavefront's o are 16 cb .. + 15, its i half of the K
+    {
+      const __bf16* AT = l == 0 ? sm.a0t : sm.at[l == 0 ? 0 : l - 1];
+      bf16x8 bf[2];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) bf[ks] = *(const bf16x8*)(dqt + col * LDT + 32 * ks + kq);
+#pragma unroll
+      for (int t = 0; t < K / 32; ++t) {
+        const int ib = rh * (K / 32) + t;
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+          acc = mfma(*(const bf16x8*)(AT + (16 * ib + lc) * LDT + 32 * ks + kq), bf[ks], acc);
+        *(floatx4*)(G + offW(l) + col * K + 16 * ib + 4 * lg) = acc;
       }
     }
     if (l == 0) break;
-    // dh_{l-1}[r][i] = sum_o dq[r][o] W_l[o][i]: (TR x HD) x (HD x HD), B from the transposed copy
-    floatx4 acc[8];
+    // dh_{l-1}[r][i] = sum_o dq[r][o] W_l[o][i]: (TR x HD) x (HD x HD)
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    {
-      const __bf16* Wt = net.wt + offW(l);  // [i][o]
-      const int row = wave * 16 + (lane & 15);
-      for (int k0 = 0; k0 < HD; k0 += 32) {
-        const bf16x8 af = frag_rows(sm.dq, HD, row, k0 + 8 * (lane >> 4));
+    for (int ks = 0; ks < HD / 32; ++ks)
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) {
-          const int i = cb * 16 + (lane & 15);
-          const bf16x8 bf = *(const bf16x8*)(Wt + i * HD + k0 + 8 * (lane >> 4));
-          acc[cb] = mfma(af, bf, acc[cb]);
-        }
-      }
-    }
-    __syncthreads();  // everyone is done with dq and ds of layer l
+      for (int j = 0; j < 2; ++j)
+        acc[j] = mfma(*(const bf16x8*)(dq + (32 * rh + 16 * j + lc) * LDH + 32 * ks + kq), wt[ks], acc[j]);
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-      const int i = cb * 16 + (lane & 15);
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int rr = wave * 16 + 4 * (lane >> 4) + v;
-        sm.ds[rr * HD + i] = acc[cb][v] * silu_grad(sbuf[((l - 1) * TR + rr) * HD + i]);
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// The tiles' partial gradients are summed in slices of kSlice tiles (tiles
-// s kSlice .. s kSlice + kSlice - 1 in order, the sum written over the
-// slice's first tile), then the slice sums in order: a fixed order, so the
-// gradient is deterministic, with kSlice times more threads at work than one
-// sum per parameter.
-constexpr int kSlice = 32;
-__global__ void slice_grad_kernel(float* part, int n_tiles) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  const int t0 = blockIdx.y * kSlice, t1 = t0 + kSlice < n_tiles ? t0 + kSlice : n_tiles;
-  if (p >= NP) return;
-  float acc = 0.f;
-  for (int t = t0; t < t1; ++t) acc += part[(int64_t)t * NP + p];
-  part[(int64_t)t0 * NP + p] = acc;
-}
-
-// grad[p] = sum over slices of the slice sums (fixed order), loss = sum part_loss * scale.
-__global__ void reduce_grad_kernel(const float* part, int n_tiles, float* grad, const float* part_loss,
-                                   float* loss, float scale) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < NP) {
-    float acc = 0.f;
-    for (int t = 0; t < n_tiles; t += kSlice) acc += part[(int64_t)t * NP + p];
-    grad[p] = acc;
-  }
-  if (p == 0 && loss) {
-    float acc = 0.f;
-    for (int t = 0; t < n_tiles; ++t) acc += part_loss[t];
-    *loss = acc * scale;
+      for (int v = 0; v < 4; ++v) ds[j][v] = acc[j][v] * silu_grad(s[l == 0 ? 0 : l - 1][j][v]);
   }
 }
 
 // Adam on the binary32 master copy, then the bfloat16 copies for the products.
-__global__ void adam_kernel(Net net, const float* grad, float lr, float b1, float b2, float eps,
-                            float c1, float c2) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NP) return;
-  const float g = grad[p];
-  const float m = b1 * net.m[p] + (1.f - b1) * g;
-  const float v = b2 * net.v[p] + (1.f - b2) * g * g;
+struct AdamStep {
+  float lr, b1, b2, eps, c1, c2;
+};
+__device__ __forceinline__ void adam_param(const Net& net, int p, float g, const AdamStep& a) {
+  const float m = a.b1 * net.m[p] + (1.f - a.b1) * g;
+  const float v = a.b2 * net.v[p] + (1.f - a.b2) * g * g;
   net.m[p] = m;
   net.v[p] = v;
-  const float w = net.p[p] - lr * (m / c1) / (sqrtf(v / c2) + eps);
+  const float w = net.p[p] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
   net.p[p] = w;
   // bfloat16 copies
   int l = 0;
@@ -460,6 +438,45 @@ __global__ void adam_kernel(Net net, const float* grad, float lr, float b1, floa
     net.wq[p] = (__bf16)w;
     net.wt[offW(l) + i * O + o] = (__bf16)w;
   }
+}
+
+// grad[p] = the sum of the tiles' partial gradients, loss = sum part_loss * scale
+// (in the last workgroup), and with ADAM the parameters' step.  A workgroup takes 64
+// parameters: wavefront w adds tiles w, w + 16, ... in order, then the first adds the
+// 16 sums in order, so the gradient is deterministic.  Bound by reading the
+// partial gradients once (55 MB for 256 tiles; two passes over slices of 32
+// tiles, the loss summed by one thread and Adam apart took 12 + 18 + 5 us).
+template <bool ADAM>
+__global__ void __launch_bounds__(1024) reduce_grad_kernel(Net net, const float* part, int n_tiles, float* grad,
+                                                           const float* part_loss, float* loss, float scale,
+                                                           AdamStep adam) {
+  __shared__ float red[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (wave != 0 || !loss) return;
+    float acc = 0.f;
+    for (int t = lane; t < n_tiles; t += 64) acc += part_loss[t];
+    for (int off = 1; off < 64; off *= 2) acc += __shfl_xor(acc, off, 64);
+    if (lane == 0) *loss = acc * scale;
+    return;
+  }
+  const int p = blockIdx.x * 64 + lane;
+  float acc = 0.f;
+  if (p < NP) {
+#pragma unroll 8
+    for (int t = wave; t < n_tiles; t += 16) acc += part[(int64_t)t * NPP + p];
+  }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave != 0 || p >= NP) return;
+  for (int w = 1; w < 16; ++w) acc += red[w][lane];
+  grad[p] = acc;
+  if constexpr (ADAM) adam_param(net, p, acc, adam);
+}
+
+__global__ void adam_kernel(Net net, const float* grad, AdamStep adam) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p < NP) adam_param(net, p, grad[p], adam);
 }
 
 __global__ void refresh_bf16_kernel(Net net) {
@@ -482,9 +499,8 @@ struct wob_mlp_s {
   Net net{};
   int64_t max_batch = 0;
   int n_tiles_max = 0;
-  float* part = nullptr;      // n_tiles_max x NP
+  float* part = nullptr;      // n_tiles_max x NPP
   float* part_loss = nullptr; // n_tiles_max
-  float* sbuf = nullptr;      // n_tiles_max x NL x TR x HD
   float* grad = nullptr;      // NP
 };
 
@@ -493,7 +509,7 @@ namespace {
 void mlp_destroy(wob_mlp_s* h) {
   if (!h) return;
   void* ptrs[] = {h->net.p, h->net.m, h->net.v, h->net.wq, h->net.wt, h->net.fourier,
-                  h->part, h->part_loss, h->sbuf, h->grad};
+                  h->part, h->part_loss, h->grad};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete h;
@@ -523,7 +539,7 @@ wob_status wob_mlp_create(int32_t dim, const float* fourier, const float* params
   if (hipFuncSetAttribute((const void*)mlp_forward_kernel,
                           hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(FwdSmem)) != hipSuccess ||
       hipFuncSetAttribute((const void*)mlp_grad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          sizeof(Smem)) != hipSuccess)
+                          sizeof(GradSmem)) != hipSuccess)
     return WOB_E_DEVICE;
   wob_mlp_s* h = new (std::nothrow) wob_mlp_s();
   if (!h) return WOB_E_ALLOC;
@@ -538,9 +554,8 @@ wob_status wob_mlp_create(int32_t dim, const float* fourier, const float* params
             hipMalloc((void**)&h->net.fourier, KF * dim * 4) == hipSuccess &&
             hipMalloc((void**)&h->grad, NP * 4) == hipSuccess;
   if (ok && h->n_tiles_max > 0)
-    ok = hipMalloc((void**)&h->part, (size_t)h->n_tiles_max * NP * 4) == hipSuccess &&
-         hipMalloc((void**)&h->part_loss, (size_t)h->n_tiles_max * 4) == hipSuccess &&
-         hipMalloc((void**)&h->sbuf, (size_t)h->n_tiles_max * NL * TR * HD * 4) == hipSuccess;
+    ok = hipMalloc((void**)&h->part, (size_t)h->n_tiles_max * NPP * 4) == hipSuccess &&
+         hipMalloc((void**)&h->part_loss, (size_t)h->n_tiles_max * 4) == hipSuccess;
   if (!ok) {
     mlp_destroy(h);
     return WOB_E_ALLOC;
@@ -605,9 +620,20 @@ wob_status wob_mlp_forward(wob_mlp h, const float* y, int64_t n, float* out, voi
   return hipGetLastError() == hipSuccess ? WOB_OK : WOB_E_DEVICE;
 }
 
-wob_status wob_mlp_backward(wob_mlp h, const float* y, const float* target,
-                            const wob_target_map* tmap, int64_t n, float* grad, float* loss,
-                            void* stream) {
+}  // extern "C"
+
+namespace {
+
+AdamStep adam_step(int64_t step, float lr, float b1, float b2, float eps) {
+  return AdamStep{lr, b1, b2, eps, 1.f - std::pow(b1, (float)step), 1.f - std::pow(b2, (float)step)};
+}
+bool valid_adam(int64_t step, float lr, float b1, float b2, float eps) {
+  return step >= 1 && lr > 0.f && std::isfinite(lr) && b1 >= 0.f && b1 < 1.f && b2 >= 0.f && b2 < 1.f && eps > 0.f;
+}
+
+// The gradient into `grad`, and with `adam` the step that it gives.
+wob_status backward(wob_mlp h, const float* y, const float* target, const wob_target_map* tmap, int64_t n,
+                    float* grad, float* loss, const AdamStep* adam, hipStream_t st) {
   if (!h || n <= 0 || n > h->max_batch || !y || !target || !grad) return WOB_E_ARG;
   TargetMap tm{0, 0.f, 1.f, 0.f};
   if (tmap) {
@@ -616,35 +642,49 @@ wob_status wob_mlp_backward(wob_mlp h, const float* y, const float* target,
       return WOB_E_ARG;
     tm = TargetMap{1, tmap->shift, 1.f / tmap->scale, tmap->clip};
   }
-  hipStream_t st = (hipStream_t)stream;
   const int tiles = (int)((n + TR - 1) / TR);
   const float scale = 1.f / (float)n;
-  hipLaunchKernelGGL(mlp_grad_kernel, dim3(tiles), dim3(NT), sizeof(Smem), st, h->net, y, target, tm,
-                     n, scale, h->part, h->part_loss, h->sbuf);
-  hipLaunchKernelGGL(slice_grad_kernel, dim3((NP + 255) / 256, (unsigned)((tiles + kSlice - 1) / kSlice)), dim3(256),
-                     0, st, h->part, (int)tiles);
-  hipLaunchKernelGGL(reduce_grad_kernel, dim3((NP + 255) / 256), dim3(256), 0, st, h->part, tiles,
-                     grad, h->part_loss, loss, scale);
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3(tiles), dim3(GT), sizeof(GradSmem), st, h->net, y, target, tm, n, scale,
+                     h->part, h->part_loss);
+  const dim3 grid((NP + 63) / 64 + 1), block(1024);
+  if (adam)
+    hipLaunchKernelGGL(reduce_grad_kernel<true>, grid, block, 0, st, h->net, h->part, tiles, grad, h->part_loss,
+                       loss, scale, *adam);
+  else
+    hipLaunchKernelGGL(reduce_grad_kernel<false>, grid, block, 0, st, h->net, h->part, tiles, grad, h->part_loss,
+                       loss, scale, AdamStep{});
   return hipGetLastError() == hipSuccess ? WOB_OK : WOB_E_DEVICE;
+}
+
+}  // namespace
+
+extern "C" {
+
+wob_status wob_mlp_backward(wob_mlp h, const float* y, const float* target,
+                            const wob_target_map* tmap, int64_t n, float* grad, float* loss,
+                            void* stream) {
+  return backward(h, y, target, tmap, n, grad, loss, nullptr, (hipStream_t)stream);
 }
 
 wob_status wob_mlp_adam_step(wob_mlp h, const float* grad, int64_t step, float lr, float b1, float b2,
                              float eps, void* stream) {
-  if (!h || !grad || step < 1 || !(lr > 0.f) || !std::isfinite(lr) || !(b1 >= 0.f && b1 < 1.f) ||
-      !(b2 >= 0.f && b2 < 1.f) || !(eps > 0.f))
-    return WOB_E_ARG;
-  const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
+  if (!h || !grad || !valid_adam(step, lr, b1, b2, eps)) return WOB_E_ARG;
   hipLaunchKernelGGL(adam_kernel, dim3((NP + 255) / 256), dim3(256), 0, (hipStream_t)stream, h->net,
-                     grad, lr, b1, b2, eps, c1, c2);
+                     grad, adam_step(step, lr, b1, b2, eps));
   return hipGetLastError() == hipSuccess ? WOB_OK : WOB_E_DEVICE;
 }
 
 wob_status wob_mlp_train_step(wob_mlp h, const float* y, const float* target,
                               const wob_target_map* tmap, int64_t n, int64_t step, float lr,
                               float* loss, void* stream) {
-  wob_status s = wob_mlp_backward(h, y, target, tmap, n, h ? h->grad : nullptr, loss, stream);
-  if (s != WOB_OK) return s;
-  return wob_mlp_adam_step(h, h->grad, step, lr, 0.9f, 0.999f, 1e-8f, stream);
+  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  if (!valid_adam(step, lr, b1, b2, eps)) {
+    // the gradient and the loss of the refused step are left as ever
+    const wob_status s = wob_mlp_backward(h, y, target, tmap, n, h ? h->grad : nullptr, loss, stream);
+    return s != WOB_OK ? s : WOB_E_ARG;
+  }
+  const AdamStep adam = adam_step(step, lr, b1, b2, eps);
+  return backward(h, y, target, tmap, n, h ? h->grad : nullptr, loss, &adam, (hipStream_t)stream);
 }
 
 }  // extern "C"
