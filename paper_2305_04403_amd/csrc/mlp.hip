@@ -24,9 +24,9 @@ constexpr int F0 = 2 * KF;    // features
 constexpr int HD = 128;       // hidden width
 constexpr int NL = 4;         // hidden layers
 constexpr int TR = 64;        // rows per workgroup
-constexpr int NT = 256;       // threads per workgroup of the forward pass (4 wavefronts)
+constexpr int NT = 512;       // threads per workgroup of the forward pass (8 wavefronts)
 constexpr int GT = 1024;      // threads per workgroup of the backward pass (16 wavefronts)
-constexpr int kFwdGrid = 1024;  // forward-pass workgroups (256 CUs x 4)
+constexpr int kFwdGrid = 512;  // forward-pass workgroups (256 CUs x the 2 resident on each)
 
 // parameter offsets (floats): W_l [out][in] then b_l, layers 0..NL (NL = output)
 constexpr int in_of(int l) { return l == 0 ? F0 : HD; }
@@ -92,6 +92,7 @@ struct FwdSmem {
   __bf16 a0[TR * LDA0];
   __bf16 act[2][TR * LDH];
   float w5[HD];  // the output layer's weights (their bfloat16 values)
+  float bias[NL][HD];
 };
 
 // The backward pass.  The weight gradients contract over the rows, so what enters
@@ -115,6 +116,7 @@ struct GradSmem {
 template <int T>
 __device__ void features_tile(const Net& net, const float* y, int64_t n, int64_t r0, __bf16* a0, int lda,
                               __bf16* a0t = nullptr) {
+#pragma unroll 1  // the binary64 sine beside a kernel's weights: two at once do not fit its registers
   for (int idx = threadIdx.x; idx < TR * KF; idx += T) {
     const int r = idx / KF, k = idx % KF;
     const int64_t row = r0 + r;
@@ -142,35 +144,35 @@ __device__ void features_tile(const Net& net, const float* y, int64_t n, int64_t
 }
 
 // Forward pass, weight-stationary: wavefront w computes output columns
-// 32 w .. 32 w + 31 of every hidden layer, and holds those columns of every
-// layer's bfloat16 weights in registers as MFMA operand fragments (26
-// fragments, 104 registers), loaded once per workgroup; the workgroups then
-// take 64-row tiles in turn.  Per layer and tile a wavefront reads the four
-// row blocks' activation fragments from LDS and issues 4 x 2 MFMAs per 32-wide
-// k step.  The accumulation order of each output (k ascending in steps of 32),
-// the bias, the activation and its rounding are those of the backward pass's
-// forward tile.
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) mlp_forward_kernel(Net net, const float* y,
+// 16 w .. 16 w + 15 of every hidden layer, and holds those columns of the first
+// layers' bfloat16 weights in registers as MFMA operand fragments (9 fragments,
+// 36 registers), loaded once per workgroup; the workgroups then take 64-row
+// tiles in turn.  The last hidden layer's fragments are loaded for each tile: with
+// them the kernel's 128 registers, four wavefronts per SIMD, spill.  Per layer
+// and tile a wavefront reads the four row blocks' activation fragments from LDS
+// and issues four MFMAs per 32-wide k step.  Bound by the activations'
+// arithmetic (about 30 lane operations each): 1,048,576 rows 398 us, and 200,992
+// rows 87 against 100 us with four wavefronts of 32 columns and all weights in
+// registers, two per SIMD.  The accumulation order of each output (k ascending
+// in steps of 32), the bias, the activation and its rounding are those of the
+// backward pass's forward tile.
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) mlp_forward_kernel(Net net, const float* y,
                                                                                         int64_t n, float* out) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   FwdSmem& sm = *reinterpret_cast<FwdSmem*>(smem_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kq = 8 * (lane >> 4);  // the lane's eight k values within a 32-wide step
-  // weight fragments: B[k][o] = W[o][k], o = 32 wave + 16 cb + lane % 16
-  bf16x8 w0[2], wh[NL - 1][2][HD / 32];
-  float bias[NL][2];
+  // weight fragments: B[k][o] = W[o][k], o = 16 wave + lane % 16
+  const int col = 16 * wave + (lane & 15);
+  const bf16x8 w0 = *(const bf16x8*)(net.wq + offW(0) + col * F0 + kq);
+  bf16x8 wh[NL - 2][HD / 32];
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    const int o = 32 * wave + 16 * cb + (lane & 15);
-    w0[cb] = *(const bf16x8*)(net.wq + offW(0) + o * F0 + kq);
+  for (int l = 1; l < NL - 1; ++l)
 #pragma unroll
-    for (int l = 1; l < NL; ++l)
-#pragma unroll
-      for (int ks = 0; ks < HD / 32; ++ks) wh[l - 1][cb][ks] = *(const bf16x8*)(net.wq + offW(l) + o * HD + 32 * ks + kq);
-#pragma unroll
-    for (int l = 0; l < NL; ++l) bias[l][cb] = net.p[offB(l) + o];
-  }
+    for (int ks = 0; ks < HD / 32; ++ks) wh[l - 1][ks] = *(const bf16x8*)(net.wq + offW(l) + col * HD + 32 * ks + kq);
   if (tid < HD) sm.w5[tid] = (float)net.wq[offW(NL) + tid];
+  static_assert(NT == NL * HD, "a bias per thread");
+  sm.bias[tid / HD][tid % HD] = net.p[offB(tid / HD) + tid % HD];
   const float b5 = net.p[offB(NL)];
   const int64_t n_tiles = (n + TR - 1) / TR;
   for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
@@ -182,36 +184,37 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) ml
       const __bf16* A = l == 0 ? sm.a0 : sm.act[(l - 1) & 1];
       const int lda = l == 0 ? LDA0 : LDH;
       __bf16* O = sm.act[l & 1];
-      floatx4 acc[4][2];
+      floatx4 acc[4];
+      bf16x8 wl[HD / 32];
+      if (l == NL - 1) {
+        const __bf16* W = net.wq;
+#ifdef __HIP_DEVICE_COMPILE__
+        asm volatile("" : "+s"(W));  // loaded for each tile, not kept across them
+#endif
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
+        for (int ks = 0; ks < HD / 32; ++ks) wl[ks] = *(const bf16x8*)(W + offW(NL - 1) + col * HD + 32 * ks + kq);
+      }
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int rb = 0; rb < 4; ++rb) acc[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < in_of(l) / 32; ++ks) {
+      for (int ks = 0; ks < in_of(l) / 32; ++ks)
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb) {
           const bf16x8 af = *(const bf16x8*)(A + (16 * rb + (lane & 15)) * lda + 32 * ks + kq);
-#pragma unroll
-          for (int cb = 0; cb < 2; ++cb) acc[rb][cb] = mfma(af, l == 0 ? w0[cb] : wh[l - 1][cb][ks], acc[rb][cb]);
+          acc[rb] = mfma(af, l == 0 ? w0 : l == NL - 1 ? wl[ks] : wh[l == 0 || l == NL - 1 ? 0 : l - 1][ks], acc[rb]);
         }
-      }
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          const int col = 32 * wave + 16 * cb + (lane & 15);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int r = 16 * rb + 4 * (lane >> 4) + v;
-            O[r * LDH + col] = (__bf16)silu_rounded(acc[rb][cb][v] + bias[l][cb]);
-          }
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * rb + 4 * (lane >> 4) + v;
+          O[r * LDH + col] = (__bf16)silu_rounded(acc[rb][v] + sm.bias[l][col]);
         }
       __syncthreads();
     }
     // output layer: 4 lanes per row, 32 terms each in order, then two butterfly
     // steps, with the weights from LDS
-    {
+    if (tid < 4 * TR) {
       const int r = tid >> 2, part = tid & 3;
       const __bf16* h4 = sm.act[(NL - 1) & 1] + r * LDH;
       float acc = 0.f;
