@@ -1501,22 +1501,21 @@ __global__ void __launch_bounds__(64 * kAddWaves) cv_addback_kernel(SceneView<R,
   for (int32_t t0 = 0; t0 < s.n_prims; t0 += kAddTile, parity ^= 1) {
     __syncthreads();
     const int32_t j = t0 + tid;
-    Far f = {{(R)0, (R)0, (R)0}, (R)0};
-    R reach = -1;  // past the last triangle: taken as far, with no weight
-    bool nonzero = false;
-    if (j < s.n_prims) {
-      const PrimGeo<R> g = load_prim<R, 3>(s, j);
-      const R gT = g_by_id[g.id];
-      nonzero = gT != (R)0;
-      R cen[3], near2;
-      addback_far<R>(g, gT, seed, cen, near2, f.y, f.gw);
-      const R d[3] = {f.y[0] - cen[0], f.y[1] - cen[1], f.y[2] - cen[2]};
-      reach = sqrt(near2) + sqrt(dot3(d, d));
-      reach = reach * reach * (R)1.0001;  // well over what the two tests' rounding can differ by
-      if (reach < (R)kAddReach) reach = (R)kAddReach;
-    }
+    // past the last triangle the tile repeats it with no weight: its test holds
+    // there too, so no pair, wherever its point lies, takes the root of zero
+    const bool real = j < s.n_prims;
+    const PrimGeo<R> g = load_prim<R, 3>(s, real ? j : s.n_prims - 1);
+    const R gT = real ? g_by_id[g.id] : (R)0;
+    const bool nonzero = gT != (R)0;
+    Far f;
+    R cen[3], near2;
+    addback_far<R>(g, gT, seed, cen, near2, f.y, f.gw);
+    if (!real) f.gw = 0;
+    const R d[3] = {f.y[0] - cen[0], f.y[1] - cen[1], f.y[2] - cen[2]};
+    R reach = sqrt(near2) + sqrt(dot3(d, d));
+    reach = reach * reach * (R)1.0001;  // well over what the two tests' rounding can differ by
     far_rec[tid] = f;
-    reach2[tid] = reach;
+    reach2[tid] = reach < (R)kAddReach ? (R)kAddReach : reach;
     const bool wave_nonzero = __ballot(nonzero) != 0;  // every lane of the wavefront votes
     if (lane == 0) vote[parity][wave] = wave_nonzero;
     __syncthreads();
@@ -1544,9 +1543,10 @@ __global__ void __launch_bounds__(64 * kAddWaves) cv_addback_kernel(SceneView<R,
       for (int k = 0; k < PPT; ++k) {
         const bool c = d2[k] < lim;
         if (!c) acc[k] += t.gw * far_rsqrt<R>(d2[k]);
-        const uint64_t mask = __ballot(c);
+        const bool take = c && q < cnt;
+        const uint64_t mask = __ballot(take);
         if (mask == 0) continue;
-        if (c) {
+        if (take) {
           const int e = held + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
           q_prim[wave][e] = t0 + q;
