@@ -31,14 +31,11 @@ namespace {
 // A workgroup holds 64 / SUB * PPL points: SUB lanes of a wavefront share PPL
 // points each and take the paths in turn, and its WAVES wavefronts split the
 // paths in as many contiguous ranges.  Bound by arithmetic where the chip is
-// full (8 instructions a pair, one of them a reciprocal square root): the split
-// over the paths is what fills it for few points.  50,000 points x 16,384
-// paths of 4 vertices took 1.92 ms with one lane per point, two points per lane,
-// four wavefronts and scalar loads of the vertices (391 workgroups for 256
-// CUs); with 16 lanes per 4 points and 8 wavefronts 0.83 ms, whole call, against
-// 1.43 with 16 wavefronts of the old form and 1.19 with 16 of the new.  At 250,000
-// points, where both fill the chip, 3.66 ms against 3.98: the vertex records
-// come from L1 four points at a time and the old form goes.
+// full (8 instructions a pair, one of them a reciprocal square root); the split
+// over the paths is what fills it for few points, and costs a reduction over
+// the lanes that few paths or many points do not pay for (see launch_gather).
+// With SUB = 1 the vertices' addresses are the same in every lane (scalar
+// loads).
 // G is accumulated without its constant factor: 3D sum w / rho, 2D sum
 // w log2(rho^2); per path the value is summed in R over chunks of
 // kGatherChunk of a lane's paths and the chunk sums in binary64.
@@ -239,13 +236,37 @@ void launch_gather_as(const R* vtx, int64_t n_paths, int32_t walk_len, const R* 
   }
 }
 
-// 128 lanes take a point's paths, 1,024 below 8 points per CU, where the first
-// leaves CUs idle (65,536 paths of 4 vertices: 1,000 points 0.38 ms against
-// 0.69, 2,000 0.52 against 0.68, 4,000 0.78 against 0.68).
+// Which split (FP32 in 3D, paths of 4 vertices; us):
+//                              8 wavefronts,      128 lanes     1,024 lanes
+//                              two points a lane  a point       a point
+//      8 paths  1,000,000 points      17             373
+//    400 paths     20,000 points      23              17             112
+//                 200,000             81             114           1,065
+//  1,600 paths        500 points      83              13              10
+//                   2,100             84              14              24
+//  4,000 paths     60,000 points     292             227             568
+//                 250,000            888             905
+//               1,000,000          3,175           3,549
+// The first needs a path for every 100 points or fewer, no more paths than
+// wavefronts, or points enough to fill the chip by themselves (1,000 per CU); with
+// a path for 20,000 points four wavefronts do (8 paths, 1,000,000 points: 13.6).
+// The last needs fewer than 8 points per CU, where the second leaves CUs idle, and
+// two paths per point and one per lane (65,536 paths: 1,000 points 380 against 690,
+// 4,000 points 780 against 680), in FP64 one per point and 256 (1,024 paths, 1,000
+// points: 12 against 26).  (50,000 points x 16,384 paths took 1.92 ms as 391
+// workgroups of 4 wavefronts, two points a lane; with 128 lanes a point the whole
+// estimate takes 1.0 instead of 3.05.)
 template <typename R, int D>
 wob_status launch_gather(const wob_scene_s* sc, const void* vtx, int64_t n_paths, int32_t walk_len,
                          const void* points, int64_t n_points, void* mean_out, void* var_out, hipStream_t st) {
-  if (n_points < (int64_t)sc->n_cu * 8)
+  constexpr int64_t least = sizeof(R) == 4 ? 1024 : 256, per_point = sizeof(R) == 4 ? 2 : 1;
+  if (n_paths <= n_points / 20000)
+    launch_gather_as<R, D, 2, 4, 1>((const R*)vtx, n_paths, walk_len, (const R*)points, n_points, (R*)mean_out,
+                                    (R*)var_out, st);
+  else if (n_paths <= 8 || n_paths <= n_points / 100 || n_points >= (int64_t)sc->n_cu * 1000)
+    launch_gather_as<R, D, 2, 8, 1>((const R*)vtx, n_paths, walk_len, (const R*)points, n_points, (R*)mean_out,
+                                    (R*)var_out, st);
+  else if (n_points < (int64_t)sc->n_cu * 8 && n_paths >= least && n_paths >= per_point * n_points)
     launch_gather_as<R, D, 4, 16, 64>((const R*)vtx, n_paths, walk_len, (const R*)points, n_points, (R*)mean_out,
                                       (R*)var_out, st);
   else
