@@ -1370,13 +1370,17 @@ walk_kernel(WalkArgs<R, D> a) {
 // pair must not cost the far ones: near needs |x - y_T| < 4 r + |y_T - c|, a bound
 // kept beside y_T; pairs within it go to a queue, and 64 of them at a time take
 // the exact centroid test and the closed form, each on a lane of its own (a
-// near pair in a wavefront's step cost all 64 lanes the closed form).  100,000
-// points x 60,976 triangles: 32 ms with four points per lane of 98 workgroups of
-// 1,024 points and the centroid test at every pair, 2.6 so (2.3e12 pairs/s; the
-// kernel's arithmetic alone allows about 4.7e12); 200,000 points 4.55, and 1.24 times
-// that with the general root at far pairs.  Tiles whose triangles all have
-// g_T = 0 add exactly zero and are skipped (the whole sum, for g = 0).
-constexpr int kAddTile = 512, kAddWaves = 8, kAddQueue = 128;
+// near pair in a wavefront's step cost all 64 lanes the closed form).  The steps
+// without a near pair are a loop of their own, which keeps the sums in place: with
+// one loop for both the compiler copied them at every step, 4 to 7 % of the time.
+// 100,000 points x 60,976 triangles: 32 ms with four points per lane of 98
+// workgroups of 1,024 points and the centroid test at every pair, 2.2 so (2.8e12
+// pairs/s; the kernel's arithmetic alone allows about 4.7e12).  Tiles whose
+// triangles all have g_T = 0 add exactly zero and are skipped, kAddVotes at a time
+// by their values alone once one is met, and a table of zeros by one look at it:
+// 200,000 points x 62,720 triangles, no value that is not zero 0.075 ms, a single
+// one 0.45 (0.70 and 0.73 with every tile taken to LDS before its vote).
+constexpr int kAddTile = 512, kAddWaves = 8, kAddQueue = 128, kAddVotes = 4;
 
 template <typename R>
 __device__ __forceinline__ R far_rsqrt(R r2) {
@@ -1450,9 +1454,9 @@ __device__ __forceinline__ R addback_pair(const SceneView<R, 3>& s, const R* g_b
 }
 
 template <typename R, int SUB, int PPT>
-__global__ void __launch_bounds__(64 * kAddWaves) cv_addback_kernel(SceneView<R, 3> s, const R* __restrict__ g_by_id,
-                                                                    const R* __restrict__ points, int64_t n,
-                                                                    uint32_t seed, R* out, int accumulate) {
+__global__ void __launch_bounds__(64 * kAddWaves) __attribute__((amdgpu_waves_per_eu(PPT <= 4 ? 6 : 4)))
+cv_addback_kernel(SceneView<R, 3> s, const R* __restrict__ g_by_id, const R* __restrict__ points, int64_t n,
+                  uint32_t seed, R* out, int accumulate) {
   constexpr int PW = 64 / SUB, PPW = PW * PPT;  // points per wavefront: at most 64
   static_assert(PPW <= 64, "a lane per point for the queued sums");
   struct alignas(4 * sizeof(R)) Far { R y[3], gw; };
@@ -1497,8 +1501,22 @@ __global__ void __launch_bounds__(64 * kAddWaves) cv_addback_kernel(SceneView<R,
     held -= m;
     __builtin_amdgcn_wave_barrier();
   };
+  // whether a wavefront of the workgroup holds a non-zero value, or the bits of
+  // kAddVotes tiles of which it does (two buffers in turn: one barrier a vote)
   int parity = 0;
-  for (int32_t t0 = 0; t0 < s.n_prims; t0 += kAddTile, parity ^= 1) {
+  const auto voted = [&](int mine) {
+    parity ^= 1;
+    if (lane == 0) vote[parity][wave] = mine;
+    __syncthreads();
+    int any = 0;
+    for (int w = 0; w < kAddWaves; ++w) any |= vote[parity][w];
+    return __builtin_amdgcn_readfirstlane(any);  // the same in every lane
+  };
+  // whether g_T of the thread's triangle in a tile is not zero
+  const auto nonzero_in = [&](int32_t j) {
+    return j < s.n_prims && g_by_id[prim_record<R, 3>(s.prims, s.prim_stride, j).idkind & kIdMask] != (R)0;
+  };
+  for (int32_t t0 = 0; t0 < s.n_prims; t0 += kAddTile) {
     __syncthreads();
     const int32_t j = t0 + tid;
     // past the last triangle the tile repeats it with no weight: its test holds
@@ -1516,40 +1534,59 @@ __global__ void __launch_bounds__(64 * kAddWaves) cv_addback_kernel(SceneView<R,
     reach = reach * reach * (R)1.0001;  // well over what the two tests' rounding can differ by
     far_rec[tid] = f;
     reach2[tid] = reach < (R)kAddReach ? (R)kAddReach : reach;
-    const bool wave_nonzero = __ballot(nonzero) != 0;  // every lane of the wavefront votes
-    if (lane == 0) vote[parity][wave] = wave_nonzero;
-    __syncthreads();
-    int any = 0;
-    for (int w = 0; w < kAddWaves; ++w) any |= vote[parity][w];
-    if (!any) continue;  // the same decision in every lane
-    const int cnt = s.n_prims - t0 < kAddTile ? s.n_prims - t0 : kAddTile;
-    for (int q = sub; q - sub < cnt; q += SUB) {
-      const Far t = far_rec[q];
-      const R lim = reach2[q];
-      bool close = false;
-      R d2[PPT];
-#pragma unroll
-      for (int k = 0; k < PPT; ++k) {
-        const R yx = t.y[0] - x[k][0], yy = t.y[1] - x[k][1], yz = t.y[2] - x[k][2];
-        d2[k] = yx * yx + yy * yy + yz * yz;
-        close = close || d2[k] < lim;
+    if (!voted(__ballot(nonzero) != 0)) {  // every lane of the wavefront votes
+      // a tile of zeros.  A table that begins with one may be all zeros, which
+      // its values in order tell soonest; else on to the next tile that is not,
+      // by the weights alone
+      if (t0 == 0) {
+        bool seen = false;
+#pragma unroll 8
+        for (int32_t i = tid; i < s.n_prims; i += kAddTile) seen = seen || g_by_id[i] != (R)0;
+        if (!voted(__ballot(seen) != 0)) break;
       }
-      if (__ballot(close) == 0) {
+      int32_t next = t0 + kAddTile;
+      while (next < s.n_prims) {
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < kAddVotes; ++i) mine |= __ballot(nonzero_in(next + i * kAddTile + tid)) != 0 ? 1 << i : 0;
+        const int tiles = voted(mine);
+        next += (tiles != 0 ? __builtin_ctz(tiles) : kAddVotes) * kAddTile;
+        if (tiles != 0) break;
+      }
+      t0 = next - kAddTile;
+      continue;
+    }
+    const int cnt = s.n_prims - t0 < kAddTile ? s.n_prims - t0 : kAddTile;
+    for (int q0 = 0; q0 < cnt; q0 += SUB) {
+      Far t;
+      R lim, d2[PPT];
+      // the steps in which no pair is near, in a loop of their own
+      for (; q0 < cnt; q0 += SUB) {
+        t = far_rec[q0 + sub];
+        lim = reach2[q0 + sub];
+        bool close = false;
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) {
+          const R yx = t.y[0] - x[k][0], yy = t.y[1] - x[k][1], yz = t.y[2] - x[k][2];
+          d2[k] = yx * yx + yy * yy + yz * yz;
+          close = close || d2[k] < lim;
+        }
+        if (__ballot(close) != 0) break;
 #pragma unroll
         for (int k = 0; k < PPT; ++k) acc[k] += t.gw * far_rsqrt<R>(d2[k]);
-        continue;
       }
+      if (q0 >= cnt) break;
 #pragma unroll
       for (int k = 0; k < PPT; ++k) {
         const bool c = d2[k] < lim;
         if (!c) acc[k] += t.gw * far_rsqrt<R>(d2[k]);
-        const bool take = c && q < cnt;
+        const bool take = c && q0 + sub < cnt;
         const uint64_t mask = __ballot(take);
         if (mask == 0) continue;
         if (take) {
           const int e = held + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-          q_prim[wave][e] = t0 + q;
+          q_prim[wave][e] = t0 + q0 + sub;
           q_point[wave][e] = place + PW * k;
         }
         held += __popcll(mask);

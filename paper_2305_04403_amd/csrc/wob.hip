@@ -483,12 +483,24 @@ void launch_addback_as(const wob_scene_s* sc, const float* g, const float* point
 void launch_addback(const wob_scene_s* sc, const float* g, const void* points, int64_t n_points, uint64_t seed,
                     void* out, int accumulate, hipStream_t st) {
   // Eight points per lane halve the LDS reads of a pair, four make twice the
-  // wavefronts: 60,976 triangles, 20,000 points 1.11 against 0.88 ms, 50,000 1.51
-  // against 1.66, 200,000 4.55 against 5.32.
+  // wavefronts; fewer lanes per point mean fewer workgroups, each of which takes
+  // every triangle to LDS and looks for the table's zeros.  62,720 triangles (us):
+  //   points       4 / 64 lanes   8 / 32 lanes   8 / 16   8 / 8
+  //      20,000         667            769
+  //      60,000       1,624          1,160        1,327
+  //     200,000       4,777          3,745        3,978    3,893
+  //     256,000                      4,260        3,937    3,908
+  //     300,000                      5,268        4,879    5,856
+  // 5,120 triangles, 1,000,000 points: 2,003, 1,434, 1,325, 1,286; 20 triangles:
+  // 461, 304, 255, 234; all values zero 201, 88, 45, 23.
   if (n_points < (int64_t)sc->n_cu * 128)
     launch_addback_as<64, 4>(sc, g, (const float*)points, n_points, seed, (float*)out, accumulate, st);
-  else
+  else if (n_points < (int64_t)sc->n_cu * 1000)
     launch_addback_as<32, 8>(sc, g, (const float*)points, n_points, seed, (float*)out, accumulate, st);
+  else if (n_points < (int64_t)sc->n_cu * 2500)
+    launch_addback_as<16, 8>(sc, g, (const float*)points, n_points, seed, (float*)out, accumulate, st);
+  else
+    launch_addback_as<8, 8>(sc, g, (const float*)points, n_points, seed, (float*)out, accumulate, st);
 }
 
 wob_status run_walk(wob_scene sc, const void* points, const int32_t* point_prim, int64_t n_points,
