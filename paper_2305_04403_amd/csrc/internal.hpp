@@ -73,20 +73,29 @@ inline int lpp_shift_for(int32_t samples, int block, bool pooled = false) {
 // workgroup, which wait for each other: up to 8 per CU (exterior Neumann, 4,000
 // points x 128 paths: 0.37 ms with 64 lanes per point, 0.48 with 128; 16
 // points x 256 paths: 1.65 ms with 32 lanes, 0.25 with 256).
-inline int spread_shift(int shift, int max_shift, int64_t n_points, int32_t samples, int32_t n_cu) {
-  while (shift < max_shift && ((int64_t)1 << shift) < samples &&
-         (n_points << shift) < (int64_t)n_cu * 64 * (shift < 6 ? 64 : 8))
-    ++shift;
+// The launch holds `others` lanes besides (the other problems of a batch), which
+// are taken to be doubled likewise; there, up to 16 wavefronts per CU while a lane
+// keeps two paths or more (four problems of 1,000 points x 1,024 paths, direct BIE:
+// 2.03 ms with 64 lanes per point, 1.70 with 128).
+inline int spread_shift(int shift, int max_shift, int64_t n_points, int32_t samples, int32_t n_cu,
+                        int64_t others = 0) {
+  for (int64_t lanes = (n_points << shift) + others;
+       shift < max_shift && ((int64_t)1 << shift) < samples; lanes *= 2, ++shift) {
+    const int per_cu = shift < 6 ? 64 : others > 0 && ((int64_t)4 << shift) <= samples ? 16 : 8;
+    if (lanes >= (int64_t)n_cu * 64 * per_cu) break;
+  }
   // a launch takes less than 2^32 lanes
   while (shift > 0 && (n_points << shift) >> 31) --shift;
   return shift;
 }
 
-// The lanes of a point of a plain solve, in a launch of its own and in a batch
-// alike (so the two merge their statistics in the same order): `spread` where
-// the walk leaves the pools of two points or takes more than a wavefront per
-// point, in workgroups of up to 256 or kWideBlock lanes, as the LDS of the scene's
-// stacks allows.
+// The lanes of a point of a plain solve: `spread` where the walk leaves the pools
+// of two points or takes more than a wavefront per point, in workgroups of up to
+// 256 or kWideBlock lanes, as the LDS of the scene's stacks allows.  `others`: the
+// lanes of the other problems of a batch, before any spread.  A spread point's
+// lanes wait for its longest path, which costs more than it gives where the other
+// problems fill the chip (64 problems of 1,000 points x 256 paths, direct BIE:
+// 12.8 ms with the lanes that each would take alone, 5.5 so).
 template <typename R>
 constexpr int kWideBlock = sizeof(R) == 4 ? 1024 : 512;
 
@@ -96,13 +105,14 @@ struct LaneSplit {
 };
 
 template <typename R>
-LaneSplit split_lanes(bool pooled, int32_t stack_cap, int64_t n_points, int32_t samples, int32_t n_cu) {
+LaneSplit split_lanes(bool pooled, int32_t stack_cap, int64_t n_points, int32_t samples, int32_t n_cu,
+                      int64_t others = 0) {
   constexpr size_t lds_limit = 160 * 1024 - 1024;
   const int most = wob::walk_lds_bytes(stack_cap, kWideBlock<R>) <= lds_limit ? (kWideBlock<R> == 1024 ? 10 : 9)
                    : wob::walk_lds_bytes(stack_cap, 256) <= lds_limit         ? 8
                                                                               : 6;
   const int shift0 = lpp_shift_for(samples, kSolveBlock, pooled);
-  const int shift = spread_shift(shift0, most, n_points, samples, n_cu);
+  const int shift = spread_shift(shift0, most, n_points, samples, n_cu, others);
   return {shift, shift > shift0 && (pooled || shift > 6)};
 }
 
