@@ -271,8 +271,10 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
   for (int64_t j = 0; j < T; ++j) {
     const int32_t id = bvh.order[j];
     leaf_of_id[id] = (int32_t)j;
-    Prim& p = *reinterpret_cast<Prim*>(recs.data() + (size_t)j * stride);
-    R* const nrm = wide ? reinterpret_cast<R*>(recs.data() + (size_t)j * stride + sizeof(Prim)) : &normals[4 * (size_t)j];
+    // written whole into the byte array, which need not be aligned for them
+    Prim p;
+    std::memset(&p, 0, sizeof(Prim));
+    R nrm[4] = {0, 0, 0, 0};
     const int32_t* ix = prims + (int64_t)id * D;
     const int k = kind ? kind[id] : 0;
     p.idkind = id | (k << wob::kIdBits);
@@ -305,6 +307,10 @@ wob_status upload_scene(wob_scene_s* sc, const std::vector<double>& v, const int
       nrm[1] = (R)(-e1d[0] / l);
       area[id] = l;
     }
+    unsigned char* const rec = recs.data() + (size_t)j * stride;
+    std::memcpy(rec, &p, sizeof(Prim));
+    if (wide) std::memcpy(rec + sizeof(Prim), nrm, sizeof(nrm));
+    else std::memcpy(&normals[4 * (size_t)j], nrm, sizeof(nrm));
   }
   sc->node_bytes = sizeof(Node);
   sc->prim_bytes = (int64_t)stride;

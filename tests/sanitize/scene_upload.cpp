@@ -1,0 +1,116 @@
+// The scene upload's host side (wob.hip: validation, records, trees, guide) on the
+// CPU, under sanitizers: the HIP runtime below keeps "device" memory on the heap,
+// checks that every copy lies inside an allocation, and launches nothing.  Prints "ok", or the first violation.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <random>
+#include <vector>
+
+#include "../../include/wob.h"
+#include "../../paper_2305_04403_amd/csrc/internal.hpp"
+
+static std::map<char*, size_t> on_device;
+static hipError_t last = hipSuccess;
+static int launches = 0;
+
+static void fail(const char* what) {
+  std::printf("%s\n", what);
+  std::exit(1);
+}
+static bool inside(const void* p, size_t n) {
+  for (const auto& a : on_device)
+    if ((const char*)p >= a.first && (const char*)p + n <= a.first + a.second) return true;
+  return false;
+}
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  // 256-byte aligned, as the device's
+  *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
+  on_device[(char*)*p] = n;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  if (on_device.erase((char*)p) != 1) fail("hipFree of what hipMalloc did not give");
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* to, const void* from, size_t n, hipMemcpyKind kind, hipStream_t) {
+  if (kind == hipMemcpyHostToDevice && !inside(to, n)) fail("copy past an allocation");
+  std::memcpy(to, from, n);
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t) {
+  if (!inside(p, n)) fail("fill past an allocation");
+  std::memset(p, v, n);
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) {
+  const hipError_t e = last;
+  last = hipSuccess;
+  return e;
+}
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return ++launches, hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipUnregisterFatBinary(void**) {}
+wob_status wob_mlp_forward(wob_mlp, const float*, int64_t, float*, void*) { return WOB_E_DEVICE; }
+}
+namespace wobi {
+OrderLayout order_layout(int, int, int64_t) { return OrderLayout{}; }
+wob_status order_points(int, int, const OrderLayout&, void*, const void*, const int32_t*, int64_t, void*, OrderBuffers*) {
+  return WOB_E_DEVICE;
+}
+wob_status scatter_results(int, const OrderBuffers&, int64_t, void*, void*, void*) { return WOB_E_DEVICE; }
+}  // namespace wobi
+
+// A strip of n random primitives (2D: segments; 3D: triangles).
+static void mesh(int dim, int n, std::vector<double>& v, std::vector<int32_t>& p) {
+  std::mt19937_64 rng(n * 10 + dim);
+  std::uniform_real_distribution<double> u(-1.0, 1.0);
+  v.resize((size_t)(n + dim - 1) * dim);
+  for (double& x : v) x = u(rng);
+  p.resize((size_t)n * dim);
+  for (int i = 0; i < n; ++i)
+    for (int c = 0; c < dim; ++c) p[(size_t)i * dim + c] = i + c;
+}
+
+static wob_scene build(int dim, int precision, int n, wob_status* s) {
+  std::vector<double> v;
+  std::vector<int32_t> p;
+  mesh(dim, n, v, p);
+  std::vector<uint8_t> kind(n);
+  std::vector<double> alpha(n, 0.5);
+  for (int i = 0; i < n; ++i) kind[i] = (uint8_t)(i % 3);
+  wob_scene sc = nullptr;
+  *s = wob_build_bvh(dim, precision, v.data(), (int64_t)v.size() / dim, p.data(), n, kind.data(), alpha.data(), &sc);
+  return sc;
+}
+
+int main() {
+  for (int dim = 2; dim <= 3; ++dim)
+    for (int precision : {WOB_F32, WOB_F64})
+      for (int n : {1, 2, 3, 5, 64, 1000, 40001, 60000}) {
+        wob_status s;
+        wob_scene sc = build(dim, precision, n, &s);
+        if (s != WOB_OK || last != hipSuccess) fail("a scene was refused");
+        wob_scene_info info;
+        wob_get_scene_info(sc, &info);
+        size_t held = 0;
+        for (const auto& a : on_device) held += a.second;
+        if ((size_t)info.device_bytes != held) fail("device_bytes is not what the scene holds");
+        wob_free(sc);
+        if (!on_device.empty()) fail("memory left by a scene");
+      }
+  std::printf("ok\n");
+}
