@@ -77,6 +77,10 @@ __device__ __forceinline__ GuideBucket guide_bucket(const GuideEntry* guide, uin
 }
 template <typename R> struct alignas(16) Prim2 { R v0[2]; R e[2]; R alpha; int32_t idkind; };
 
+// Values per unit normal in an array of their own (FP32 triangles: four, one load).
+template <typename R, int D>
+constexpr int kNormalValues = D == 3 && sizeof(R) == 4 ? 4 : D;
+
 template <typename R, int D> struct Rec;
 template <typename R> struct Rec<R, 3> { using Node = Wide<R>; using Prim = Prim3<R>; };
 template <typename R> struct Rec<R, 2> { using Node = Wide<R>; using Prim = Prim2<R>; };
@@ -87,15 +91,15 @@ constexpr int32_t kIdMask = (1 << kIdBits) - 1;
 template <typename R, int D>
 struct SceneView {
   const typename Rec<R, D>::Node* nodes;
-  // primitive records and unit outward normals (4 values, the last 0) in leaf
-  // order, each a fixed number of bytes apart
+  // primitive records and unit outward normals in leaf order, each a fixed number
+  // of bytes apart
   const char* prims;
   const char* normals;
   uint32_t prim_stride, normal_stride;
   const int32_t* leaf_of_id;  // caller id -> leaf-order index
   const float* area_cdf;      // caller-id order, cumulative area / |Gamma| (binary32, last 1)
   const GuideEntry* area_guide;  // 2^guide_shift + 1 entries (the last: n_prims - 1)
-  const Candidate<R>* candidates;  // caller-id order
+  const Candidate<R>* candidates;  // caller-id order (pinned host memory where the device had none left)
   int32_t guide_shift;
   R area_total;               // |Gamma|
   int32_t n_nodes;            // interior records

@@ -27,6 +27,7 @@ struct wob_scene_s {
   float* d_area_cdf = nullptr;  // caller-id order, cumulative area / total (last entry 1)
   wob::GuideEntry* d_area_guide = nullptr;  // 2^guide_shift + 1 entries: the search range of each bucket
   void* d_candidates = nullptr;  // RIS candidates, caller-id order
+  bool candidates_on_host = false;  // in pinned host memory
   int32_t guide_shift = 0;
   unsigned long long* d_status = nullptr;  // non-finite path values excluded from solves (sticky)
   double area_total = 0.0;      // |Gamma|
@@ -124,7 +125,7 @@ wob::SceneView<R, D> view(const wob_scene_s* sc) {
   s.prim_stride = (uint32_t)sc->prim_bytes;
   // beside the records, or an array of their own
   s.normals = sc->d_normals ? (const char*)sc->d_normals : (const char*)sc->d_prims + sc->normal_offset;
-  s.normal_stride = sc->d_normals ? (uint32_t)(4 * sizeof(R)) : (uint32_t)sc->prim_bytes;
+  s.normal_stride = sc->d_normals ? (uint32_t)(wob::kNormalValues<R, D> * sizeof(R)) : (uint32_t)sc->prim_bytes;
   s.leaf_of_id = sc->d_leaf_of_id;
   s.area_cdf = sc->d_area_cdf;
   s.area_guide = sc->d_area_guide;

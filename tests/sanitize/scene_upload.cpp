@@ -1,6 +1,7 @@
 // The scene upload's host side (wob.hip: validation, records, trees, guide) on the
 // CPU, under sanitizers: the HIP runtime below keeps "device" memory on the heap,
-// checks that every copy lies inside an allocation, and launches nothing.  Prints "ok", or the first violation.
+// checks that every copy lies inside an allocation, launches nothing, and can refuse
+// an allocation.  Prints "ok", or the first violation.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -14,10 +15,16 @@
 #include "../../include/wob.h"
 #include "../../paper_2305_04403_amd/csrc/internal.hpp"
 
-static std::map<char*, size_t> on_device;
+static std::map<char*, size_t> on_device, on_host;
+static int asked = 0, refuse = -1;  // allocations so far, and which to refuse
+static size_t last_size = 0;
 static hipError_t last = hipSuccess;
 static int launches = 0;
 
+static hipError_t set(hipError_t e) {
+  if (e != hipSuccess) last = e;
+  return e;
+}
 static void fail(const char* what) {
   std::printf("%s\n", what);
   std::exit(1);
@@ -30,6 +37,8 @@ static bool inside(const void* p, size_t n) {
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+  last_size = n;
+  if (asked++ == refuse) return set(hipErrorOutOfMemory);
   // 256-byte aligned, as the device's
   *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
   on_device[(char*)*p] = n;
@@ -37,6 +46,16 @@ hipError_t hipMalloc(void** p, size_t n) {
 }
 hipError_t hipFree(void* p) {
   if (on_device.erase((char*)p) != 1) fail("hipFree of what hipMalloc did not give");
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
+  on_host[(char*)*p] = n;
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  if (on_host.erase((char*)p) != 1) fail("hipHostFree of what hipHostMalloc did not give");
   std::free(p);
   return hipSuccess;
 }
@@ -102,6 +121,7 @@ int main() {
     for (int precision : {WOB_F32, WOB_F64})
       for (int n : {1, 2, 3, 5, 64, 1000, 40001, 60000}) {
         wob_status s;
+        asked = 0;
         wob_scene sc = build(dim, precision, n, &s);
         if (s != WOB_OK || last != hipSuccess) fail("a scene was refused");
         wob_scene_info info;
@@ -110,7 +130,22 @@ int main() {
         for (const auto& a : on_device) held += a.second;
         if ((size_t)info.device_bytes != held) fail("device_bytes is not what the scene holds");
         wob_free(sc);
-        if (!on_device.empty()) fail("memory left by a scene");
+        if (!on_device.empty() || !on_host.empty()) fail("memory left by a scene");
+
+        // no device memory for the RIS candidates: the scene has them on the host
+        const size_t per = precision == WOB_F32 ? 64 : 128;
+        if (last_size != per * n) fail("the candidates' table is not the last allocation");
+        refuse = asked - 1;
+        asked = 0;
+        sc = build(dim, precision, n, &s);
+        refuse = -1;
+        if (s != WOB_OK) fail("a scene without room for its candidates was refused");
+        if (hipGetLastError() != hipSuccess) fail("the refused allocation is left as an error");
+        if (on_host.size() != 1 || on_host.begin()->second != per * n) fail("no candidates on the host");
+        wob_get_scene_info(sc, &info);
+        if ((size_t)info.device_bytes != held - per * n) fail("device_bytes counts host memory");
+        wob_free(sc);
+        if (!on_device.empty() || !on_host.empty()) fail("memory left by a scene with candidates on the host");
       }
   std::printf("ok\n");
 }
