@@ -432,12 +432,16 @@ void launch_form(const wob::WalkArgs<R, D>& a0, int mode, int32_t n_cu, hipStrea
   const int ppb = B >> a.lpp_shift;
   const dim3 grid((unsigned)((a.n_points + ppb - 1) / ppb)), block(B);
   size_t lds = wob::walk_lds_bytes(a.scene.stack_cap, B);  // traversal stacks, held leaves
-  // the double layer on a scene well beyond an XCD's 4 MB of L2: 14 wavefronts
-  // per CU instead of 17 fetch less over each other (200,000-triangle sphere,
-  // 100k points x 128 paths: 20.8 ms against 22.6; 98,000 triangles 17.9 against
-  // 18.0; the 20,480-triangle slice, within L2, 57.5 against 51.1, and the other
+  // the FP32 double layer on a scene of triangles well beyond an XCD's 4 MB of L2: 14
+  // wavefronts per CU instead of 17 fetch less over each other, but end later, which
+  // costs more with few paths per lane (100,000 points, 17 against 14 wavefronts, ms:
+  // 200,000 triangles x 128 / 256 / 512 paths 20.6 / 42.1 / 86.5 against 21.6 / 40.3 /
+  // 77.7; 144,500 18.5 / 37.2 / 75.7 against 20.1 / 37.8 / 72.7; 120,000 segments
+  // x 256 58.0 against 64.4; FP64, of fewer wavefronts anyway, the same; the other
   // forms, which run four wavefronts per SIMD or fewer, lose everywhere)
-  if (FORM == wob::F_DL && mode == MODE_SOLVE && !a0.grad_out && a0.scene.n_prims > kPackedPrims * 5 / 2)
+  if (D == 3 && sizeof(R) == 4 && FORM == wob::F_DL && mode == MODE_SOLVE && !a0.grad_out &&
+      (int64_t)a.N >= (int64_t)(a0.scene.n_prims > kPackedPrims * 4 ? 4 : 8) << a.lpp_shift &&
+      a0.scene.n_prims > kPackedPrims * 3)
     lds = std::max(lds, (size_t)kLargeSceneLds);
   if constexpr (FORM != wob::F_FWD) {
     if (a.grad_out || a.path_grad_out) {  // value and gradient along the same paths

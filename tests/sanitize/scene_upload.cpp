@@ -1,7 +1,8 @@
-// The scene upload's host side (wob.hip: validation, records, trees, guide) on the
-// CPU, under sanitizers: the HIP runtime below keeps "device" memory on the heap,
-// checks that every copy lies inside an allocation, launches nothing, and can refuse
-// an allocation.  Prints "ok", or the first violation.
+// The host side of the scene upload and of the solve's launch (wob.hip: validation,
+// records, trees, guide, launch shapes) on the CPU, under sanitizers: the HIP runtime
+// below keeps "device" memory on the heap, checks that every copy lies inside an
+// allocation, launches nothing, and can refuse an allocation.  Prints "ok", or the
+// first violation.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -19,6 +20,11 @@ static std::map<char*, size_t> on_device, on_host;
 static int asked = 0, refuse = -1;  // allocations so far, and which to refuse
 static size_t last_size = 0;
 static hipError_t last = hipSuccess;
+static struct {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t stream;
+} config;
 static int launches = 0;
 
 static hipError_t set(hipError_t e) {
@@ -78,8 +84,14 @@ hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return ++launches, hipSuccess; }
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t st) {
+  config = {g, b, lds, st};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* st) {
+  *g = config.grid, *b = config.block, *lds = config.lds, *st = config.stream;
+  return hipSuccess;
+}
 void** __hipRegisterFatBinary(const void*) { return nullptr; }
 void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
 void __hipUnregisterFatBinary(void**) {}
@@ -104,19 +116,52 @@ static void mesh(int dim, int n, std::vector<double>& v, std::vector<int32_t>& p
     for (int c = 0; c < dim; ++c) p[(size_t)i * dim + c] = i + c;
 }
 
-static wob_scene build(int dim, int precision, int n, wob_status* s) {
+static wob_scene build(int dim, int precision, int n, wob_status* s, bool dirichlet = false) {
   std::vector<double> v;
   std::vector<int32_t> p;
   mesh(dim, n, v, p);
   std::vector<uint8_t> kind(n);
   std::vector<double> alpha(n, 0.5);
-  for (int i = 0; i < n; ++i) kind[i] = (uint8_t)(i % 3);
+  for (int i = 0; i < n; ++i) kind[i] = (uint8_t)(dirichlet ? 0 : i % 3);
   wob_scene sc = nullptr;
   *s = wob_build_bvh(dim, precision, v.data(), (int64_t)v.size() / dim, p.data(), n, kind.data(), alpha.data(), &sc);
   return sc;
 }
 
+// Dynamic LDS of a double-layer solve beyond what its stacks take.
+static long extra_lds(wob_scene sc, int64_t points, int paths) {
+  std::vector<double> buffer(points * 3);
+  wob_bc bc;
+  std::memset(&bc, 0, sizeof(bc));
+  bc.domain = 1;
+  bc.formulation = WOB_F_DOUBLE_LAYER;
+  if (wob_solve(sc, buffer.data(), nullptr, points, &bc, paths, 4, 0, buffer.data(), nullptr, nullptr) != WOB_OK)
+    fail("a solve was refused");
+  return (long)config.lds - (long)wob::walk_lds_bytes(sc->stack_cap, (int)config.block.x);
+}
+
+// Fewer wavefronts for the double layer: large FP32 scenes of triangles and several
+// paths per lane alone.
+static void check_lds() {
+  struct { int dim, precision, n; int64_t points; int paths; bool more; } const cases[] = {
+      {3, WOB_F32, 165000, 100000, 256, true}, {3, WOB_F32, 165000, 100000, 128, false},
+      {3, WOB_F32, 165000, 100000, 16, false}, {3, WOB_F32, 125000, 100000, 512, true},
+      {3, WOB_F32, 125000, 100000, 256, false}, {3, WOB_F32, 110000, 100000, 512, false},
+      {2, WOB_F32, 165000, 100000, 256, false}, {3, WOB_F64, 165000, 100000, 256, false}};
+  for (const auto& c : cases) {
+    wob_status s;
+    wob_scene sc = build(c.dim, c.precision, c.n, &s, true);
+    if (s != WOB_OK) fail("a scene was refused");
+    if ((extra_lds(sc, c.points, c.paths) > 0) != c.more) {
+      std::printf("%dD precision %d, %d primitives, %d paths: ", c.dim, c.precision, c.n, c.paths);
+      fail("LDS beyond the stacks");
+    }
+    wob_free(sc);
+  }
+}
+
 int main() {
+  check_lds();
   for (int dim = 2; dim <= 3; ++dim)
     for (int precision : {WOB_F32, WOB_F64})
       for (int n : {1, 2, 3, 5, 64, 1000, 40001, 60000}) {
