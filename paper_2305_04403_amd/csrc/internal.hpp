@@ -58,7 +58,7 @@ constexpr int kPathsPerLane = 2;
 // when that is below 64), and at most 32 for solves whose lane groups pool
 // two points (wob::pools_points: a group of 2 x 32 lanes is one wavefront)
 inline int lpp_shift_for(int32_t samples, int block, bool pooled = false) {
-  const int32_t lanes = (samples + kPathsPerLane - 1) / kPathsPerLane;
+  const int32_t lanes = (samples - 1) / kPathsPerLane + 1;
   const int cap = pooled ? (block < 32 ? block : 32) : block;
   int s = 0;
   while ((1 << s) < lanes && (1 << s) < cap) ++s;
@@ -114,7 +114,7 @@ LaneSplit split_lanes(bool pooled, int32_t stack_cap, int64_t n_points, int32_t 
                                                                               : 6;
   const int shift0 = lpp_shift_for(samples, kSolveBlock, pooled);
   const int shift = spread_shift(shift0, most, n_points, samples, n_cu, others);
-  return {shift, shift > shift0 && (pooled || shift > 6)};
+  return {shift, (shift > shift0 && (pooled || shift > 6)) || (pooled && samples >= wob::kMaxPooled)};
 }
 
 template <typename R, int D>

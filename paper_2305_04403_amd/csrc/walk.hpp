@@ -940,6 +940,28 @@ __device__ __forceinline__ void chan_merge(double& n, double& mean, double& m2, 
 template <int EXT, int D>
 constexpr int red_stride() { return ext_kind(EXT) == X_GRAD ? 3 + 2 * D : 3; }
 
+// Counter c of a group of G = 2^gshift lanes -> the path's index k among the N of
+// its point and, in a pool, which of the two points (pl); false past the group's
+// last path.  Counters are taken in increasing order, and so are the paths they name;
+// a group takes at most G past the last one.  `lane`: one of the group's, of the
+// point's lpp.  In 32 bits for any N < 2^31 (pooled: below kMaxPooled, so that 2 N
+// counters and those past them fit).
+constexpr int32_t kMaxPooled = 1 << 30;
+template <bool POOL>
+__host__ __device__ __forceinline__ bool group_path(uint32_t c, const int32_t& N, int G, int gshift, int lpp,
+                                                    int lane, int& pl, int& k) {
+  if constexpr (POOL) {
+    pl = c >= (uint32_t)N ? 1 : 0;
+    k = (int)(c - (uint32_t)pl * (uint32_t)N);
+    return c < 2u * (uint32_t)N;
+  } else {
+    pl = 0;
+    const uint32_t at = (uint32_t)(lane & ~(G - 1)) + (c & (uint32_t)(G - 1)) + (c >> gshift) * (uint32_t)lpp;
+    k = (int)at;
+    return at < (uint32_t)N;
+  }
+}
+
 template <typename R, int D, int FORM, bool TRACE, bool COUNT, int BLOCK, int EXT = X_NONE, bool PARTS = false>
 __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t block_index, double* red, int part = 0) {
   const int tid = threadIdx.x;
@@ -964,19 +986,9 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
   // writes the same value before it reads it.
   int32_t* const offset_word = wob_stack + (kStackRow + a.scene.stack_cap + 1) * BLOCK;
   if ((tid & 63) == 0) *offset_word = a.path_offset;
-  // counter c of the group -> the path's point (0 or 1 within the pool) and
-  // index; false past the group's last path (c is taken in increasing order,
-  // and so are the paths it names)
-  auto path_of = [&](int c, int& pl_, int& k_) -> bool {
-    if constexpr (POOL) {
-      pl_ = c >= a.N ? 1 : 0;
-      k_ = c - pl_ * a.N;
-      return c < 2 * a.N && point0 + pl_ < a.n_points;
-    } else {
-      pl_ = 0;
-      k_ = (lane_in_point & ~(G - 1)) + (c & (G - 1)) + (c >> gshift) * lpp;
-      return k_ < a.N && point0 < a.n_points;
-    }
+  // counter c of the group -> its path; false past the last one
+  auto path_of = [&](uint32_t c, int& pl_, int& k_) -> bool {
+    return group_path<POOL>(c, a.N, G, gshift, lpp, lane_in_point, pl_, k_) && point0 + pl_ < a.n_points;
   };
   double n = 0.0, mean = 0.0, m2 = 0.0;
   // pooled: the statistics of the pool's second point
@@ -1128,8 +1140,11 @@ __device__ __forceinline__ void walk_block(const WalkArgs<R, D>& a, int64_t bloc
             // load may be hoisted out of this loop and kept in a register that
             // only the writing lane updates (stale counters, repeated paths)
             int32_t* const gnext = wob_stack + kCounterRow * BLOCK + (tid & ~(G - 1));
-            const int c = __hip_atomic_load(gnext, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + rank;
-            if (rank == 0) __hip_atomic_store(gnext, c + __popcll(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            const uint32_t c =
+                (uint32_t)__hip_atomic_load(gnext, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT) + (uint32_t)rank;
+            if (rank == 0)
+              __hip_atomic_store(gnext, (int32_t)(c + (uint32_t)__popcll(mine)), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WAVEFRONT);
             int pn;
             go = path_of(c, pn, k);
             if (POOL && go && pn != pl) {  // the pool's second point: its data
