@@ -95,8 +95,8 @@ wob_status fill_table(const wob_problem* probs, const int32_t* order, int n, int
     // the double layer takes the lanes that it would take alone: a batch of nothing
     // else gains 3 % by fewer (64 problems of 1,000 points x 256 paths 11.0 ms, one
     // of all their points 10.7), and its statistics are merged in the same order
-    const LaneSplit split = split_lanes<R>(pooled, p.scene->stack_cap, p.n_points, p.samples, n_cu,
-                                           a.form == wob::F_DL ? 0 : lanes - own);
+    const LaneSplit split = split_lanes<R, D>(a.form, pooled, p.scene->stack_cap, p.n_points, p.samples, n_cu,
+                                              a.form == wob::F_DL ? 0 : lanes - own);
     a.lpp_shift = split.shift;
     if (split.spread) a.form |= wob::kFormSpread;
     const int64_t ppt = std::max(1, block >> a.lpp_shift);

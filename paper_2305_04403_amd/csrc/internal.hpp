@@ -78,11 +78,18 @@ inline int lpp_shift_for(int32_t samples, int block, bool pooled = false) {
 // are taken to be doubled likewise; there, up to 16 wavefronts per CU while a lane
 // keeps two paths or more (four problems of 1,000 points x 1,024 paths, direct BIE:
 // 2.03 ms with 64 lanes per point, 1.70 with 128).
-inline int spread_shift(int shift, int max_shift, int64_t n_points, int32_t samples, int32_t n_cu,
-                        int64_t others = 0) {
+// FP64 walks of the single layer and the direct BIE by lines, of two wavefronts per
+// SIMD, are no longer short of them at 8 per CU (direct BIE x 64 paths, 28,125 points
+// 2.02 ms with 32 lanes per point, 3.22 with 64; 7,812 points 0.62 against 0.98), in 2D
+// at 16 (28,125 points 0.92 against 1.31; 7,812 x 200 paths, single layer, 0.69 with
+// 32, 0.64 with 64).
+template <typename R, int D>
+int spread_shift(int form, int shift, int max_shift, int64_t n_points, int32_t samples, int32_t n_cu,
+                 int64_t others = 0) {
+  const int first = sizeof(R) == 8 && (form == wob::F_SL || form == wob::F_DIRECT) ? (D == 3 ? 8 : 16) : 64;
   for (int64_t lanes = (n_points << shift) + others;
        shift < max_shift && ((int64_t)1 << shift) < samples; lanes *= 2, ++shift) {
-    const int per_cu = shift < 6 ? 64 : others > 0 && ((int64_t)4 << shift) <= samples ? 16 : 8;
+    const int per_cu = shift < 6 ? first : others > 0 && ((int64_t)4 << shift) <= samples ? 16 : 8;
     if (lanes >= (int64_t)n_cu * 64 * per_cu) break;
   }
   // a launch takes less than 2^32 lanes
@@ -105,15 +112,15 @@ struct LaneSplit {
   bool spread;
 };
 
-template <typename R>
-LaneSplit split_lanes(bool pooled, int32_t stack_cap, int64_t n_points, int32_t samples, int32_t n_cu,
+template <typename R, int D>
+LaneSplit split_lanes(int form, bool pooled, int32_t stack_cap, int64_t n_points, int32_t samples, int32_t n_cu,
                       int64_t others = 0) {
   constexpr size_t lds_limit = 160 * 1024 - 1024;
   const int most = wob::walk_lds_bytes(stack_cap, kWideBlock<R>) <= lds_limit ? (kWideBlock<R> == 1024 ? 10 : 9)
                    : wob::walk_lds_bytes(stack_cap, 256) <= lds_limit         ? 8
                                                                               : 6;
   const int shift0 = lpp_shift_for(samples, kSolveBlock, pooled);
-  const int shift = spread_shift(shift0, most, n_points, samples, n_cu, others);
+  const int shift = spread_shift<R, D>(form, shift0, most, n_points, samples, n_cu, others);
   return {shift, (shift > shift0 && (pooled || shift > 6)) || (pooled && samples >= wob::kMaxPooled)};
 }
 

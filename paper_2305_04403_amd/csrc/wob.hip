@@ -418,7 +418,7 @@ void launch_form(const wob::WalkArgs<R, D>& a0, int mode, int32_t n_cu, hipStrea
   const bool pooled = plain && wob::pools_points(FORM, VX, false, false);
   wob::WalkArgs<R, D> a = a0;
   if (plain) {
-    const LaneSplit split = split_lanes<R>(pooled, a.scene.stack_cap, a.n_points, a.N, n_cu);
+    const LaneSplit split = split_lanes<R, D>(FORM, pooled, a.scene.stack_cap, a.n_points, a.N, n_cu);
     a.lpp_shift = split.shift;
     if (split.spread) {
       if (split.shift <= 6) launch_spread<R, D, FORM, VX, 64>(a, st);
@@ -427,7 +427,7 @@ void launch_form(const wob::WalkArgs<R, D>& a0, int mode, int32_t n_cu, hipStrea
       return;
     }
   } else {
-    a.lpp_shift = spread_shift(lpp_shift_for(a.N, B), 6, a.n_points, a.N, n_cu);
+    a.lpp_shift = spread_shift<R, D>(FORM, lpp_shift_for(a.N, B), 6, a.n_points, a.N, n_cu);
   }
   const int ppb = B >> a.lpp_shift;
   const dim3 grid((unsigned)((a.n_points + ppb - 1) / ppb)), block(B);

@@ -56,7 +56,7 @@ int main() {
   // and a launch never pools more
   for (const int64_t points : {1, 1000, 100000000})
     for (const int32_t N : {(1 << 30) - 1, 1 << 30, most})
-      if (!wobi::split_lanes<float>(true, 17, points, N, 256).spread && N >= wob::kMaxPooled)
+      if (!wobi::split_lanes<float, 3>(wob::F_SL, true, 17, points, N, 256).spread && N >= wob::kMaxPooled)
         return bad("pooled", N, 0);
   std::printf("ok\n");
 }
