@@ -78,18 +78,24 @@ inline int lpp_shift_for(int32_t samples, int block, bool pooled = false) {
 // are taken to be doubled likewise; there, up to 16 wavefronts per CU while a lane
 // keeps two paths or more (four problems of 1,000 points x 1,024 paths, direct BIE:
 // 2.03 ms with 64 lanes per point, 1.70 with 128).
-// FP64 walks of the single layer and the direct BIE by lines, of two wavefronts per
-// SIMD, are no longer short of them at 8 per CU (direct BIE x 64 paths, 28,125 points
-// 2.02 ms with 32 lanes per point, 3.22 with 64; 7,812 points 0.62 against 0.98), in 2D
-// at 16 (28,125 points 0.92 against 1.31; 7,812 x 200 paths, single layer, 0.69 with
-// 32, 0.64 with 64).
+// Walks of the single layer and the direct BIE by lines, whose paths differ most in
+// length (many lines miss), take one path per lane only up to 8 wavefronts per CU:
+// beyond, the lanes that wait cost more (direct BIE on 62,720 triangles, 28,125 points
+// x 64 paths 1.24 ms with 32 lanes per point, 1.83 with 64; 7,812 points 0.39 against
+// 0.59).  In FP64, of two wavefronts per SIMD, no doubling pays beyond 8 (direct BIE,
+// 28,125 points x 64 paths 2.02 ms against 3.22; 7,812 points 0.62 against 0.98), in
+// 2D beyond 16 (28,125 points 0.92 against 1.31; 7,812 x 200 paths, single layer, 0.69
+// with 32 lanes, 0.64 with 64).
 template <typename R, int D>
 int spread_shift(int form, int shift, int max_shift, int64_t n_points, int32_t samples, int32_t n_cu,
                  int64_t others = 0) {
-  const int first = sizeof(R) == 8 && (form == wob::F_SL || form == wob::F_DIRECT) ? (D == 3 ? 8 : 16) : 64;
+  const bool uneven = form == wob::F_SL || form == wob::F_DIRECT;
   for (int64_t lanes = (n_points << shift) + others;
        shift < max_shift && ((int64_t)1 << shift) < samples; lanes *= 2, ++shift) {
-    const int per_cu = shift < 6 ? first : others > 0 && ((int64_t)4 << shift) <= samples ? 16 : 8;
+    int per_cu = 64;
+    if (shift >= 6) per_cu = others > 0 && ((int64_t)4 << shift) <= samples ? 16 : 8;
+    else if (uneven && sizeof(R) == 8) per_cu = D == 3 ? 8 : 16;
+    else if (uneven && samples <= 2 << shift) per_cu = 8;
     if (lanes >= (int64_t)n_cu * 64 * per_cu) break;
   }
   // a launch takes less than 2^32 lanes

@@ -1,6 +1,6 @@
-"""FP64 walks by lines at sizes around the rule for their lanes per point: twice the
-points take about twice the time, whichever side of the rule they lie on, and the
-statistics are those of the traced paths."""
+"""Walks by lines at sizes around the rule for their lanes per point: the time follows
+the points, whichever side of the rule they lie on, and the statistics are those of
+the traced paths."""
 import time
 
 import numpy as np
@@ -35,10 +35,12 @@ def seconds(call):
     return best
 
 
-def problem(W, form):
+def problem(W, form, precision="f64"):
     mesh = I.perturb_radial(I.icosphere(24), 0.1, 3, 4)
     mesh = I.Mesh(3, mesh.verts, mesh.prims, np.full(mesh.n_prims, I.NEUMANN, np.uint8))
-    return W.Scene(mesh, W.F64), W.BC(-1, 2 if form == "direct" else 3, W.PROG_INVDIST, (0.2, -0.1, 0.05))
+    if precision == "f32":
+        mesh = mesh.as_float32_geometry()
+    return W.Scene(mesh, W.F64 if precision == "f64" else W.F32), W.BC(-1, 2 if form == "direct" else 3, W.PROG_INVDIST, (0.2, -0.1, 0.05))
 
 
 @pytest.mark.parametrize("form", ["direct", "single"])
@@ -48,6 +50,17 @@ def test_time_follows_the_points(W, form):
     t = {n: seconds(lambda: W.solve(scene, pts[:n], bc, 64, 4, 1)) for n in (30_000, 120_000)}
     # a quarter of the points: no more than 0.32 of the time
     assert t[30_000] < 0.32 * t[120_000], t
+    scene.close()
+
+
+@pytest.mark.parametrize("form", ["direct", "single"])
+def test_time_follows_the_points_f32(W, form):
+    scene, bc = problem(W, form, "f32")
+    pts = dev(I.ball_points(120_000, 2.0, 5, r_min=1.2), torch.float32)
+    t = {n: seconds(lambda: W.solve(scene, pts[:n], bc, 64, 4, 1)) for n in (30_000, 120_000)}
+    # a quarter of the points: no more than 0.36 of the time (the last wavefronts'
+    # end weighs more than in FP64)
+    assert t[30_000] < 0.36 * t[120_000], t
     scene.close()
 
 
