@@ -54,7 +54,7 @@ constexpr int32_t kEnd = INT32_MAX;
 constexpr int kMaxDepth = 60;
 // FP32 triangle records lie 48 bytes apart in small scenes, and 64 in large
 // ones, where each then holds its unit normal in the last 16 bytes and never
-// straddles a 64-byte block (see prim_layout in the scene upload).
+// straddles a 64-byte block (kPackedPrims in the scene upload).
 template <typename R> struct alignas(sizeof(R) == 4 ? 16 : 32) Prim3 { R v0[3]; int32_t idkind; R e1[3]; R alpha; R e2[3]; int32_t pad; };
 // One primitive as a RIS candidate: all that its evaluation and, if it is
 // picked, the vertex on it need, in one 64-byte line (FP32), in caller-id order

@@ -42,7 +42,7 @@ struct WalkArgs {
   R self_p;                   // floor(p_s 2^24) / 2^24
   uint32_t k0, k1;            // Philox key
   uint32_t problem;           // problem index (counter word 2, bits 24..31)
-  int32_t lpp_shift;          // log2 of lanes per point (0 .. log2 of the block size)
+  int32_t lpp_shift;          // log2 of lanes per point: up to the block, and up to 10 where a batch walks a point in parts
   int32_t path_offset;        // path k of a point draws the random numbers of path path_offset + k
   int32_t form;               // F_DL / F_DIRECT / F_SL / F_SL_RIS, | kFormSpread (read by the batched kernel)
   int32_t density;            // estimate the boundary unknown at boundary points (no own emission)
@@ -1546,7 +1546,11 @@ cv_addback_kernel(SceneView<R, 3> s, const R* __restrict__ g_by_id, const R* __r
     if (!real) f.gw = 0;
     const R d[3] = {f.y[0] - cen[0], f.y[1] - cen[1], f.y[2] - cen[2]};
     R reach = sqrt(near2) + sqrt(dot3(d, d));
-    reach = reach * reach * (R)1.0001;  // well over what the two tests' rounding can differ by
+    // both tests take single differences of the same three points, whose errors are
+    // relative: the squares and sums differ by some 12 of their 2^-24 (a point that
+    // the compiler forms otherwise in the two places moves a pair at 4 r by its own
+    // rounding, where either form is right)
+    reach = reach * reach * (R)1.0001;
     far_rec[tid] = f;
     reach2[tid] = reach < (R)kAddReach ? (R)kAddReach : reach;
     if (!voted(__ballot(nonzero) != 0)) {  // every lane of the wavefront votes
