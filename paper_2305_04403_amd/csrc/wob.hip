@@ -624,8 +624,8 @@ namespace {
 wob_status build_scene(int32_t dim, int32_t precision, const double* verts, int64_t n_verts,
                        const int32_t* prims, int64_t n_prims, const uint8_t* kind, const double* alpha,
                        hipStream_t st, wob_scene* out) {
-  // vertices rounded to the scene precision: both the walk and any external
-  // checker then see the same geometry
+  // vertices rounded to the scene precision: the walk and the oracle then see the
+  // same geometry
   std::vector<double> v((size_t)(n_verts * dim));
   for (int64_t i = 0; i < n_verts * dim; ++i) {
     const double x = verts[i];
